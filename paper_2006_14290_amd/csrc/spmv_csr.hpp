@@ -13,6 +13,7 @@ constexpr int kRowThreads = 256;  // row-per-subwarp kernel: work-group size
 constexpr int kRowU = 4;          // rows per subwarp in the row-per-subwarp kernel
 constexpr int kRowIters = 8;      // row groups per work-group in the row-per-subwarp kernel
 constexpr int kRowMaxRows = 65536;  // larger matrices take the load-balanced kernel
+constexpr int64_t kStageMinNnz = 8192;  // staged-rows kernel: fewer entries take the load-balanced kernel
 
 inline int64_t csr_tiles(int64_t nnz) { return nnz > 0 ? ceil_div(nnz, kCsrTile) : 1; }
 
