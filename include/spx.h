@@ -346,7 +346,7 @@ spx_status spx_bicg_solve(const spx_matrix *A, const double *b, double *x, const
 /* Pipelined preconditioned CG (Ghysels & Vanroose, Parallel Computing
  * 40(7), 2014): CG's iterates in exact arithmetic with one reduction phase
  * per iteration that does not wait for the product with A; three launches
- * per iteration against CG's five, more vector traffic. precond 0 or 1, any
+ * per iteration, as CG, and more vector traffic. precond 0 or 1, any
  * matrix format. info->spmv_count includes the product w = A u of every
  * (re)start. Breakdown: p.Ap <= 0 (the step's denominator). Otherwise as
  * spx_cg_solve (BLOCKING, same errors). */

@@ -31,8 +31,6 @@ enum KFlag : int32_t {
 enum KOp : int32_t {
     kOpNone = 0,
     kOpCgInit,     // t0 = b.b, t1 = r.z, t2 = r.r
-    kOpCgAlpha,    // t0 = p.q
-    kOpCgRho,      // t0 = r.z, t1 = r.r
     kOpBiInit,     // t0 = b.b, t1 = r.r
     kOpBiAlpha,    // t0 = rhat.v
     kOpBiS,        // t0 = s.s
@@ -71,25 +69,6 @@ __device__ inline void finish_op(int op, const double *t, KState *st)
         if (!finite(t[0]) || !finite(t[2])) st->flag = kNonfinite;
         else if (t[0] == 0.0) st->flag = kZeroRhs;
         else if (t[2] <= st->tol2 * t[0]) st->flag = kConverged;
-        break;
-    case kOpCgAlpha:
-        if (!finite(t[0])) st->flag = kNonfinite;
-        else if (t[0] <= 0.0) st->flag = kBreakdown;
-        else st->alpha = st->rho / t[0];
-        break;
-    case kOpCgRho:
-        st->iters += 1;
-        st->spmv_count += 1;
-        st->rr = t[1];
-        if (!finite(t[1]) || !finite(t[0])) {
-            st->flag = kNonfinite;
-        } else if (t[1] <= st->tol2 * st->bb) {
-            st->flag = kConverged;
-        } else {
-            st->beta = t[0] / st->rho;
-            st->rho = t[0];
-            if (st->iters >= st->maxit) st->flag = kMaxit;
-        }
         break;
     case kOpBiInit:
         st->bb = t[0];
@@ -236,6 +215,26 @@ __device__ __forceinline__ T block_sum(T v, T *s_red)
     T t = T(0);
     if (threadIdx.x == 0)
         for (int w = 0; w < kThreads / kWave; ++w) t += s_red[w];
+    __syncthreads();
+    return t;
+}
+
+// Sum of n partials, in every thread of the work-group (all must call):
+// thread t adds partials t, t + kThreads, ... in float64, then the wavefront
+// sums and the wavefronts' sums in order. Every work-group that sums the same
+// partials gets the same bits.
+template <typename T, int kThreads>
+__device__ __forceinline__ double block_sum_partials(const T *__restrict__ partials, int n, double *s_sum)
+{
+    double acc = 0.0;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n; i += kThreads) acc += (double)partials[i];
+    acc = wave_sum(acc);
+    if (lane_id() == 0) s_sum[threadIdx.x / kWave] = acc;
+    __syncthreads();
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kThreads / kWave; ++w) t += s_sum[w];
     __syncthreads();
     return t;
 }

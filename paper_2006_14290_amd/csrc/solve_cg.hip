@@ -2,13 +2,14 @@
 //
 // Textbook PCG (Hestenes & Stiefel 1952; the preconditioned form of Barrett
 // et al., "Templates", 1994) with a scalar Jacobi preconditioner, the solver
-// the paper benchmarks in Section 4. One iteration is five launches:
-//   1. q = A p fused with the partial sums of p.q (CSR and SELL-P epilogue;
-//      a separate dot kernel for the other formats);
-//   2. a one-work-group finisher sums them in a fixed order: alpha = rho / p.q;
-//   3. x += alpha p, r -= alpha q, z = D^{-1} r, partial sums of r.z and r.r;
-//   4. a finisher forms beta and tests ||r|| <= tol ||b||;
-//   5. p = z + beta p.
+// the paper benchmarks in Section 4. One iteration is three launches:
+//   1. q = A p fused with the partial sums of p.q (CSR, ELL and SELL-P
+//      epilogue; a separate dot kernel for the other formats);
+//   2. alpha = rho / p.q, r -= alpha q, partial sums of r.r and r.z
+//      (z = D^{-1} r is not stored; block Jacobi forms it in one more launch);
+//   3. x += alpha p, beta and the test ||r|| <= tol ||b||, p = z + beta p.
+// Every work-group of 2 and 3 sums the partials of the launch before it in
+// the same fixed order.
 // Scalars never leave the device; a block of `check_every` iterations is
 // captured once into a hipGraph and replayed, and the host reads the state
 // only between replays. When the recursive residual passes, the true residual
@@ -24,8 +25,23 @@
 #include "small_cg.hpp"
 #include "solver_common.hpp"
 #include "solvers.hpp"
+#include "vec_io.hpp"
 
 namespace spx {
+
+// The fields of the state that an iteration reads, into another buffer.
+__device__ __forceinline__ void cg_commit(const KState *in, KState *out, double rho, double rr, int32_t flag,
+                                          int32_t iters, int32_t spmv_count)
+{
+    out->rho = rho;
+    out->rr = rr;
+    out->bb = in->bb;
+    out->tol2 = in->tol2;
+    out->maxit = in->maxit;
+    out->flag = flag;
+    out->iters = iters;
+    out->spmv_count = spmv_count;
+}
 
 template <typename X>
 __global__ __launch_bounds__(kVecThreads) void cg_init_kernel(int64_t n, const X *__restrict__ b,
@@ -56,70 +72,129 @@ __global__ __launch_bounds__(kVecThreads) void cg_init_kernel(int64_t n, const X
     write_partials<X, 3>(v, partials, gridDim.x, blockIdx.x);
 }
 
-// Each thread takes kVecItems consecutive entries: one 16/32-byte load per
-// vector when kVec (all pointers suitably aligned), else element by element.
-template <typename X, bool kVec>
-__global__ __launch_bounds__(kVecThreads) void cg_update_kernel(int64_t n, X *__restrict__ x, const X *__restrict__ p,
-                                                               const X *__restrict__ q, X *__restrict__ r,
-                                                               X *__restrict__ z, const X *__restrict__ dinv,
-                                                               X *__restrict__ partials, KState *st)
+// One iteration's two vector kernels. Both first sum the partials that the
+// kernel before them left (every work-group the same ones in the same order,
+// so all take the same decisions) instead of waiting for a one-work-group
+// finisher in between; the loads of their first vectors are in flight
+// meanwhile. At most kCgBlocks work-groups, so that the partials stay few
+// (1,024 values: 8 KB per work-group and row, from L2). What bounds them: the
+// vectors. Against the five-launch iteration (product, finisher, update,
+// finisher, direction), on one MI355X: Jacobi on the anisotropic 128^3 grid 82
+// -> 73 us per iteration (z is not stored: one vector pass less), the 64^3
+// 7-point grid 25 -> 20, the 257^2 grid 14 -> 10.5.
+constexpr int kCgBlocks = 1024;
+
+inline int64_t cg_blocks(int64_t n)
+{
+    const int64_t b = vec_blocks(n);
+    return b < kCgBlocks ? b : kCgBlocks;
+}
+
+// How z = M^{-1} r comes about: z = r, z = r * dinv, or z a vector of its own
+// (block Jacobi).
+enum CgPre : int { kCgNone = 0, kCgJacobi = 1, kCgBlock = 2 };
+
+// alpha = rho / p.q; r -= alpha q; partials of r.r (and of r.z for kCgJacobi).
+// The first work-group records alpha, or why there is none, for the second
+// kernel (no work-group of this launch reads those two fields).
+template <typename X, CgPre kPre>
+__global__ __launch_bounds__(kVecThreads) void cg_residual_kernel(int64_t n, const X *__restrict__ pq, int npq,
+                                                                 const X *__restrict__ q, X *__restrict__ r,
+                                                                 const X *__restrict__ dinv, X *__restrict__ rr_out,
+                                                                 X *__restrict__ rz_out, KState *st)
 {
     if (st->flag != kRunning) return;
     __shared__ X s_red[kVecThreads / kWave];
-    typedef X XV __attribute__((ext_vector_type(kVecItems)));
-    const X a = (X)st->alpha;
-    const int64_t i0 = ((int64_t)blockIdx.x * kVecThreads + threadIdx.x) * kVecItems;
+    __shared__ double s_sum[kVecThreads / kWave];
+    const int64_t step = (int64_t)gridDim.x * kVecChunk;
+    int64_t i0 = vec_i0();
+    vec4_t<X> rv = ld4<X, true>(r, i0, n), qv = ld4<X, true>(q, i0, n), dv = {};
+    if (kPre == kCgJacobi) dv = ld4<X, true>(dinv, i0, n);
+    const double t = block_sum_partials<X, kVecThreads>(pq, npq, s_sum);
+    const int32_t stop = !finite(t) ? kNonfinite : (t <= 0.0 ? kBreakdown : kRunning);
+    const double alpha = st->rho / t;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->pad0 = stop;
+        st->alpha = alpha;
+    }
+    if (stop != kRunning) return;
+    const X a = (X)alpha;
     X rz = X(0), rr = X(0);
-    if (kVec && i0 + kVecItems <= n) {
-        XV xv = *reinterpret_cast<const XV *>(x + i0);
-        const XV pv = *reinterpret_cast<const XV *>(p + i0);
-        const XV qv = *reinterpret_cast<const XV *>(q + i0);
-        XV rv = *reinterpret_cast<const XV *>(r + i0);
-        XV zv;
-        const XV dv = dinv ? *reinterpret_cast<const XV *>(dinv + i0) : XV{};
+    while (true) {
+#pragma unroll
+        for (int u = 0; u < kVecItems; ++u) {
+            rv[u] = rv[u] - a * qv[u];
+            if (kPre == kCgJacobi) rz += rv[u] * (rv[u] * dv[u]);
+            rr += rv[u] * rv[u];
+        }
+        st4<X, true>(r, i0, n, rv);
+        i0 += step;
+        if (i0 - threadIdx.x * kVecItems >= n) break;  // uniform across the work-group
+        rv = ld4<X, true>(r, i0, n);
+        qv = ld4<X, true>(q, i0, n);
+        if (kPre == kCgJacobi) dv = ld4<X, true>(dinv, i0, n);
+    }
+    X v[1] = {block_sum<X, kVecThreads>(rr, s_red)};
+    write_partials<X, 1>(v, rr_out, gridDim.x, blockIdx.x);
+    if (kPre == kCgJacobi) {
+        v[0] = block_sum<X, kVecThreads>(rz, s_red);
+        write_partials<X, 1>(v, rz_out, gridDim.x, blockIdx.x);
+    }
+}
+
+// x += alpha p; beta = r.z / rho and the convergence test; p = z + beta p.
+// The state after the iteration goes to another buffer than the one that this
+// launch's work-groups read.
+template <typename X, CgPre kPre, bool kVecX>
+__global__ __launch_bounds__(kVecThreads) void cg_direction_kernel(int64_t n, const X *__restrict__ rr_in, int nrr,
+                                                                  const X *__restrict__ rz_in, int nrz,
+                                                                  const X *__restrict__ z, const X *__restrict__ dinv,
+                                                                  X *__restrict__ x, X *__restrict__ p,
+                                                                  const KState *__restrict__ in,
+                                                                  KState *__restrict__ out)
+{
+    __shared__ double s_sum[kVecThreads / kWave];
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    int32_t flag = in->flag;
+    if (flag == kRunning) flag = in->pad0;
+    if (flag != kRunning) {
+        if (first) cg_commit(in, out, in->rho, in->rr, flag, in->iters, in->spmv_count);
+        return;
+    }
+    const int64_t step = (int64_t)gridDim.x * kVecChunk;
+    int64_t i0 = vec_i0();
+    vec4_t<X> xv = ld4<X, kVecX>(x, i0, n), pv = ld4<X, true>(p, i0, n), zv = ld4<X, true>(z, i0, n), dv = {};
+    if (kPre == kCgJacobi) dv = ld4<X, true>(dinv, i0, n);
+    const double rr = block_sum_partials<X, kVecThreads>(rr_in, nrr, s_sum);
+    const double rz = kPre == kCgNone ? rr : block_sum_partials<X, kVecThreads>(rz_in, nrz, s_sum);
+    const int32_t iters = in->iters + 1;
+    if (!finite(rr) || !finite(rz)) flag = kNonfinite;
+    else if (rr <= in->tol2 * in->bb) flag = kConverged;
+    else if (iters >= in->maxit) flag = kMaxit;
+    if (first) cg_commit(in, out, flag == kRunning || flag == kMaxit ? rz : in->rho, rr, flag, iters,
+                         in->spmv_count + 1);
+    const X a = (X)in->alpha, be = (X)(rz / in->rho);
+    while (true) {
 #pragma unroll
         for (int u = 0; u < kVecItems; ++u) {
             xv[u] += a * pv[u];
-            rv[u] = rv[u] - a * qv[u];
-            zv[u] = dinv ? rv[u] * dv[u] : rv[u];
-            rz += rv[u] * zv[u];
-            rr += rv[u] * rv[u];
+            pv[u] = (kPre == kCgJacobi ? zv[u] * dv[u] : zv[u]) + be * pv[u];
         }
-        *reinterpret_cast<XV *>(x + i0) = xv;
-        *reinterpret_cast<XV *>(r + i0) = rv;
-        if (dinv) *reinterpret_cast<XV *>(z + i0) = zv;
-    } else {
-        for (int64_t i = i0; i < i0 + kVecItems && i < n; ++i) {
-            x[i] += a * p[i];
-            const X ri = r[i] - a * q[i];
-            r[i] = ri;
-            const X zi = dinv ? ri * dinv[i] : ri;
-            if (dinv) z[i] = zi;
-            rz += ri * zi;
-            rr += ri * ri;
-        }
+        st4<X, kVecX>(x, i0, n, xv);
+        if (flag == kRunning) st4<X, true>(p, i0, n, pv);
+        i0 += step;
+        if (i0 - threadIdx.x * kVecItems >= n) break;
+        xv = ld4<X, kVecX>(x, i0, n);
+        pv = ld4<X, true>(p, i0, n);
+        zv = ld4<X, true>(z, i0, n);
+        if (kPre == kCgJacobi) dv = ld4<X, true>(dinv, i0, n);
     }
-    X v[2] = {block_sum<X, kVecThreads>(rz, s_red), block_sum<X, kVecThreads>(rr, s_red)};
-    write_partials<X, 2>(v, partials, gridDim.x, blockIdx.x);
 }
 
-template <typename X, bool kVec>
-__global__ __launch_bounds__(kVecThreads) void cg_p_kernel(int64_t n, const X *__restrict__ z, X *__restrict__ p,
-                                                          const KState *st)
+// After an odd number of iterations: the state back to the first buffer.
+__global__ void cg_state_copy_kernel(const KState *__restrict__ in, KState *__restrict__ out)
 {
-    if (st->flag != kRunning) return;
-    typedef X XV __attribute__((ext_vector_type(kVecItems)));
-    const X be = (X)st->beta;
-    const int64_t i0 = ((int64_t)blockIdx.x * kVecThreads + threadIdx.x) * kVecItems;
-    if (kVec && i0 + kVecItems <= n) {
-        const XV zv = *reinterpret_cast<const XV *>(z + i0);
-        XV pv = *reinterpret_cast<const XV *>(p + i0);
-#pragma unroll
-        for (int u = 0; u < kVecItems; ++u) pv[u] = zv[u] + be * pv[u];
-        *reinterpret_cast<XV *>(p + i0) = pv;
-    } else {
-        for (int64_t i = i0; i < i0 + kVecItems && i < n; ++i) p[i] = z[i] + be * p[i];
-    }
+    if (threadIdx.x == 0) cg_commit(in, out, in->rho, in->rr, in->flag, in->iters, in->spmv_count);
 }
 
 template <typename X>
@@ -166,7 +241,7 @@ static CgBufs<V, X> cg_carve(Carve &c, const spx_matrix &A, int precond)
 {
     const int64_t n = A.nrows;
     CgBufs<V, X> w{};
-    w.st = c.take<KState>(1);
+    w.st = c.take<KState>(2);
     w.r = c.take<X>(n);
     w.p = c.take<X>(n);
     w.q = c.take<X>(n);
@@ -290,25 +365,48 @@ spx_status cg_run(const spx_matrix &A_in, const X *b, X *x, const SolveSpec &sp,
     // vector loads need every vector aligned to kVecItems entries (x is the
     // caller's; the workspace pieces are 256-byte aligned)
     const bool vec = (reinterpret_cast<uintptr_t>(x) % (kVecItems * sizeof(X))) == 0;
+    const int64_t slots = partial_slots(A);
+    X *rr_parts = w.partials + slots, *rz_parts = w.partials + 2 * slots;
+    const unsigned gc = (unsigned)cg_blocks(n);
+    const int nrz = bs ? (int)gv : (int)gc;
+#define SPX_CG_RESIDUAL(PRE)                                                                                   \
+    cg_residual_kernel<X, PRE><<<gc, kVecThreads, 0, s>>>(n, w.partials, (int)npq, w.q, w.r, w.dinv, rr_parts, \
+                                                          rz_parts, in)
+#define SPX_CG_DIRECTION(PRE, VEC)                                                                                   \
+    cg_direction_kernel<X, PRE, VEC><<<gc, kVecThreads, 0, s>>>(n, rr_parts, (int)gc, rz_parts, nrz, bs ? w.z : w.r, \
+                                                                w.dinv, x, w.p, in, out)
     auto iterations = [&]() -> spx_status {
+        KState *in = w.st, *out = w.st + 1;
         for (int it = 0; it < m; ++it) {
-            SPX_CHECK((spmv_dot<V, X>(A, w.p, w.q, w.p, w.partials, w.st, kOpCgAlpha, s)));
-            if (vec) {
-                cg_update_kernel<X, true><<<gv, kVecThreads, 0, s>>>(n, x, w.p, w.q, w.r, sp.precond ? w.z : nullptr,
-                                                                    w.dinv, w.partials, w.st);
+            int64_t npq = 0;
+            SPX_CHECK((spmv_dot_partials<V, X>(A, w.p, w.q, w.p, w.partials, in, &npq, s)));
+            if (sp.precond == 1) SPX_CG_RESIDUAL(kCgJacobi);
+            else SPX_CG_RESIDUAL(kCgNone);
+            // block Jacobi: z = M^{-1} r and the r.z partials
+            if (bs) SPX_CHECK(bj_apply<X>(n, bs, w.inv, w.r, w.z, nullptr, rz_parts, 0, in, true, s));
+            if (bs) {
+                if (vec) SPX_CG_DIRECTION(kCgBlock, true);
+                else SPX_CG_DIRECTION(kCgBlock, false);
+            } else if (sp.precond == 1) {
+                if (vec) SPX_CG_DIRECTION(kCgJacobi, true);
+                else SPX_CG_DIRECTION(kCgJacobi, false);
             } else {
-                cg_update_kernel<X, false><<<gv, kVecThreads, 0, s>>>(n, x, w.p, w.q, w.r,
-                                                                     sp.precond ? w.z : nullptr, w.dinv, w.partials,
-                                                                     w.st);
+                if (vec) SPX_CG_DIRECTION(kCgNone, true);
+                else SPX_CG_DIRECTION(kCgNone, false);
             }
-            // block Jacobi: z = M^{-1} r and the r.z partials replace row 0
-            if (bs) SPX_CHECK(bj_apply<X>(n, bs, w.inv, w.r, w.z, nullptr, w.partials, 0, w.st, true, s));
-            SPX_CHECK(launch_finish<X>(w.partials, gv, 2, w.st, kOpCgRho, s));
-            cg_p_kernel<X, true><<<gv, kVecThreads, 0, s>>>(n, w.z, w.p, w.st);
+            SPX_LAUNCHED();
+            KState *t = in;
+            in = out;
+            out = t;
+        }
+        if (m % 2) {
+            cg_state_copy_kernel<<<1, kWave, 0, s>>>(in, out);
             SPX_LAUNCHED();
         }
         return SPX_OK;
     };
+#undef SPX_CG_RESIDUAL
+#undef SPX_CG_DIRECTION
     spx_status status = SPX_OK;
     bool have_true = false;
     double true2 = 0.0;

@@ -268,25 +268,51 @@ __global__ __launch_bounds__(kVecThreads) void residual_kernel(int64_t n, const 
 }
 
 template <typename V, typename X>
+static spx_status product_dot(const spx_matrix &A, const X *p, X *q, const X *w, X *partials, const KState *st_in,
+                              int64_t *nparts, hipStream_t stream)
+{
+    KState *st = const_cast<KState *>(st_in);  // read only: the launches take it as the flag to skip on
+    *nparts = spmv_dot_parts(A);
+    if (A.fmt == SPX_CSR) return csr_spmv_launch<V, X>(A, p, q, X(1), X(0), w, partials, stream, 1, st);
+    if (A.fmt == SPX_SELLP) return sellp_spmv_launch<V, X>(A, p, q, X(1), X(0), stream, 1, w, partials, st);
+    if (A.fmt == SPX_ELL) return ell_spmv_launch<V, X>(A, p, q, X(1), X(0), stream, 1, w, partials, st);
+    SPX_CHECK(spmv_dispatch(A, p, q, 1.0, 0.0, stream));
+    dot_kernel<X><<<(unsigned)vec_blocks(A.nrows), kVecThreads, 0, stream>>>(A.nrows, w, q, partials, st, 0);
+    SPX_LAUNCHED();
+    return SPX_OK;
+}
+
+template <typename V, typename X>
 spx_status spmv_dot(const spx_matrix &A, const X *p, X *q, const X *w, X *partials, KState *st, int op,
                     hipStream_t stream)
 {
-    if (A.fmt == SPX_CSR) {
-        SPX_CHECK((csr_spmv_launch<V, X>(A, p, q, X(1), X(0), w, partials, stream, 1, st, op)));
-        return launch_finish<X>(partials, csr_dot_parts(A), 1, st, op, stream);
+    int64_t nparts = 0;
+    SPX_CHECK((product_dot<V, X>(A, p, q, w, partials, st, &nparts, stream)));
+    return launch_finish<X>(partials, nparts, 1, st, op, stream);
+}
+
+// partials[0] = the sum of all n (one work-group, fixed order).
+template <typename X>
+__global__ __launch_bounds__(kFinThreads) void reduce_partials_kernel(X *__restrict__ partials, int n,
+                                                                     const KState *st)
+{
+    if (st->flag != kRunning) return;
+    __shared__ double s_sum[kFinThreads / kWave];
+    const double t = block_sum_partials<X, kFinThreads>(partials, n, s_sum);
+    if (threadIdx.x == 0) partials[0] = (X)t;
+}
+
+template <typename V, typename X>
+spx_status spmv_dot_partials(const spx_matrix &A, const X *p, X *q, const X *w, X *partials, const KState *st,
+                             int64_t *nparts, hipStream_t stream)
+{
+    SPX_CHECK((product_dot<V, X>(A, p, q, w, partials, st, nparts, stream)));
+    if (*nparts > kMaxParts) {
+        reduce_partials_kernel<X><<<1, kFinThreads, 0, stream>>>(partials, (int)*nparts, st);
+        SPX_LAUNCHED();
+        *nparts = 1;
     }
-    if (A.fmt == SPX_SELLP) {
-        SPX_CHECK((sellp_spmv_launch<V, X>(A, p, q, X(1), X(0), stream, 1, w, partials, st)));
-        return launch_finish<X>(partials, spmv_dot_parts(A), 1, st, op, stream);
-    }
-    if (A.fmt == SPX_ELL) {
-        SPX_CHECK((ell_spmv_launch<V, X>(A, p, q, X(1), X(0), stream, 1, w, partials, st)));
-        return launch_finish<X>(partials, spmv_dot_parts(A), 1, st, op, stream);
-    }
-    SPX_CHECK(spmv_dispatch(A, p, q, 1.0, 0.0, stream));
-    dot_kernel<X><<<(unsigned)vec_blocks(A.nrows), kVecThreads, 0, stream>>>(A.nrows, w, q, partials, st, op);
-    SPX_LAUNCHED();
-    return launch_finish<X>(partials, vec_blocks(A.nrows), 1, st, op, stream);
+    return SPX_OK;
 }
 
 template <typename V, typename X>
@@ -329,6 +355,12 @@ template spx_status spmv_dot<float, float>(const spx_matrix &, const float *, fl
                                            int, hipStream_t);
 template spx_status spmv_dot<_Float16, float>(const spx_matrix &, const float *, float *, const float *, float *,
                                               KState *, int, hipStream_t);
+template spx_status spmv_dot_partials<double, double>(const spx_matrix &, const double *, double *, const double *,
+                                                      double *, const KState *, int64_t *, hipStream_t);
+template spx_status spmv_dot_partials<float, float>(const spx_matrix &, const float *, float *, const float *, float *,
+                                                    const KState *, int64_t *, hipStream_t);
+template spx_status spmv_dot_partials<_Float16, float>(const spx_matrix &, const float *, float *, const float *,
+                                                       float *, const KState *, int64_t *, hipStream_t);
 template spx_status spmv_dot2<double, double>(const spx_matrix &, const double *, double *, const double *, double *,
                                               KState *, int, hipStream_t);
 template spx_status residual_norm<double>(int64_t, const double *, const double *, double *, double *, KState *,

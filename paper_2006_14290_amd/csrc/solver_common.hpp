@@ -28,7 +28,10 @@ inline int64_t spmv_dot_parts(const spx_matrix &A)
 }
 inline int64_t partial_slots(const spx_matrix &A)
 {
-    const int64_t a = spmv_dot_parts(A), b = vec_blocks(A.nrows);
+    // (CSR: for whichever of its kernels the product may take)
+    int64_t a = spmv_dot_parts(A);
+    const int64_t b = vec_blocks(A.nrows), t = A.fmt == SPX_CSR ? csr_tiles(A.nnz) : 0;
+    if (t > a) a = t;
     return a > b ? a : b;
 }
 
@@ -125,6 +128,14 @@ inline spx_status status_of_flag(int32_t flag)
     default: return SPX_ERR_NOT_CONVERGED;
     }
 }
+
+// q = A p (any format) with the partials of w.q, *nparts of them at partials
+// (at most kMaxParts: more are first summed to one, so that kernels whose
+// every work-group sums them stay cheap).
+constexpr int64_t kMaxParts = 4096;
+template <typename V, typename X>
+spx_status spmv_dot_partials(const spx_matrix &A, const X *p, X *q, const X *w, X *partials, const KState *st,
+                             int64_t *nparts, hipStream_t stream);
 
 // Generic product q = A p (any format) plus the deterministic sum w.q
 // finished by `op`; CSR fuses the sum into the product's epilogue.
