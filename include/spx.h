@@ -163,13 +163,13 @@ spx_status spx_spmv(const spx_matrix *A, const void *x, void *y, double alpha, d
                     hipStream_t stream);
 
 /* Same as spx_spmv but requires fmt == SPX_CSR. Three kernels:
- *  - small matrices (at most 65536 rows) with short, even rows
+ *  - known, similar rows (at most 128 entries, the mean at least half of the
+ *    power of two at or above the longest) and at least 8192 entries: every
+ *    wavefront streams its own rows through LDS;
+ *  - other small matrices (at most 32768 rows) with short, even rows
  *    (A->max_row_len known and at most twice the power of two at or above
  *    the mean row length): one subwarp of that many lanes per row, DPP row
  *    sums;
- *  - larger matrices with known, similar rows (at most 128 entries, the mean
- *    at least half of the next power of two at or above the longest): every
- *    wavefront streams its own rows through LDS;
  *  - otherwise (or max_row_len == 0): load balanced. The rows are split into
  *    work-groups of equal nonzero count (a row is owned by the group in which
  *    it starts), so skewed row lengths stay balanced; each group stages the

@@ -53,7 +53,10 @@ __global__ __launch_bounds__(kThreads) void csr_spmv_kernel(
 // so every load instruction reads one contiguous stretch of col / val. The
 // first kSub entries of all kRowU rows are loaded before the first gather;
 // longer rows continue in a loop. Rows are reduced with DPP (fixed order).
-// A block repeats this kRowIters times over the following rows.
+// A block does this once: what bounds it is the chain of its three dependent
+// loads (row pointer, column, x), so every further step of a block would add
+// the whole chain again (4,096 rows in 4 blocks of eight steps: 13.6 us; in
+// 32 blocks of one: 3.7).
 template <typename V, typename X, int kEpi, int kSub>
 __global__ __launch_bounds__(kRowThreads) void csr_rows_kernel(
     int32_t nrows, int64_t nblocks, int64_t grid_padded, const int32_t *__restrict__ rowptr,
@@ -67,9 +70,8 @@ __global__ __launch_bounds__(kRowThreads) void csr_rows_kernel(
     if (blk >= nblocks) return;
     const int tid = threadIdx.x, sw = tid / kSub, sl = tid % kSub;
     X d1 = X(0), d2 = X(0);
-    for (int it = 0; it < kRowIters; ++it) {
-        const int64_t base = (blk * kRowIters + it) * kStep + sw;
-        if (base - sw >= nrows) break;  // uniform across the block
+    {
+        const int64_t base = blk * kStep + sw;
         int32_t a[kRowU], b[kRowU], c[kRowU];
         V v[kRowU];
 #pragma unroll
@@ -147,19 +149,6 @@ spx_status csr_partition_launch(const spx_matrix &A, int32_t *part, hipStream_t 
     return SPX_OK;
 }
 
-int csr_rows_sub(const spx_matrix &A)
-{
-    // measured on gfx950: the row-per-subwarp kernel wins only on small
-    // matrices (a few launches' worth of work, where the load-balanced
-    // kernel's staging and barriers dominate); the load-balanced kernel
-    // streams large banded matrices faster
-    if (A.nrows <= 0 || A.nrows > kRowMaxRows || A.max_row_len <= 0 || A.nnz <= 0) return 0;
-    const int64_t mean = ceil_div(A.nnz, A.nrows);
-    int sub = 4;
-    while (sub < 64 && sub < mean) sub <<= 1;
-    return A.max_row_len <= 2 * sub ? sub : 0;
-}
-
 // The staged-rows kernel (spmv_csr_stage.hpp) for A: the row length its
 // unrolled part holds (8, 16, 32, 64 or 128 entries), or 0 when A takes
 // another kernel. Rows must be known to fit that length and fill at least
@@ -174,6 +163,19 @@ static int stage_len(const spx_matrix &A)
     for (int len = 8; len <= 128; len *= 2)
         if (A.max_row_len <= len) return 2 * A.nnz >= (int64_t)len * A.nrows ? len : 0;
     return 0;
+}
+
+int csr_rows_sub(const spx_matrix &A)
+{
+    // measured on gfx950 against the tile kernel, 5 to 45 random entries per
+    // row: 3,000 rows 3.8 / 3.5 us, 20,000 rows 5.1 / 6.1, 60,000 rows 9.8 /
+    // 8.6. Below kStageMinNnz entries (1,089 rows of 5) 3.2 / 5.2.
+    if (stage_len(A) > 0) return 0;
+    if (A.nrows <= 0 || A.nrows > kRowMaxRows || A.max_row_len <= 0 || A.nnz <= 0) return 0;
+    const int64_t mean = ceil_div(A.nnz, A.nrows);
+    int sub = 4;
+    while (sub < 64 && sub < mean) sub <<= 1;
+    return A.max_row_len <= 2 * sub ? sub : 0;
 }
 
 // Rows per block, work-groups per CU and grid of the staged-rows kernel.
@@ -219,11 +221,11 @@ static void stage_launch(const spx_matrix &A, int len, const X *x, X *y, X alpha
 
 int64_t csr_dot_parts(const spx_matrix &A)
 {
-    const int sub = csr_rows_sub(A);
-    const int len = sub == 0 ? stage_len(A) : 0;
+    const int len = stage_len(A);
     if (len > 0) return stage_grid(A, len);
+    const int sub = csr_rows_sub(A);
     if (sub == 0) return csr_tiles(A.nnz);
-    return ceil_div(A.nrows, (int64_t)(kRowThreads / sub) * kRowU * kRowIters);
+    return ceil_div(A.nrows, (int64_t)(kRowThreads / sub) * kRowU);
 }
 
 template <typename V, typename X>
@@ -231,6 +233,13 @@ spx_status csr_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X bet
                            X *dot_partials, hipStream_t stream, int epi, KState *st, int op)
 {
     const V *val = static_cast<const V *>(A.vals);
+    if (const int len = stage_len(A); len > 0) {
+        if (epi == 2) stage_launch<V, X, 2>(A, len, x, y, alpha, beta, dot_with, dot_partials, stream, st);
+        else if (epi == 1) stage_launch<V, X, 1>(A, len, x, y, alpha, beta, dot_with, dot_partials, stream, st);
+        else stage_launch<V, X, 0>(A, len, x, y, alpha, beta, dot_with, dot_partials, stream, st);
+        SPX_LAUNCHED();
+        return SPX_OK;
+    }
     const int sub = csr_rows_sub(A);
     if (sub > 0) {
         const int64_t nblocks = csr_dot_parts(A);
@@ -252,13 +261,6 @@ spx_status csr_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X bet
         }
 #undef SPX_ROWS_EPI
 #undef SPX_ROWS_LAUNCH
-        SPX_LAUNCHED();
-        return SPX_OK;
-    }
-    if (const int len = stage_len(A); len > 0) {
-        if (epi == 2) stage_launch<V, X, 2>(A, len, x, y, alpha, beta, dot_with, dot_partials, stream, st);
-        else if (epi == 1) stage_launch<V, X, 1>(A, len, x, y, alpha, beta, dot_with, dot_partials, stream, st);
-        else stage_launch<V, X, 0>(A, len, x, y, alpha, beta, dot_with, dot_partials, stream, st);
         SPX_LAUNCHED();
         return SPX_OK;
     }

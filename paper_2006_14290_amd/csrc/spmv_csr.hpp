@@ -11,8 +11,7 @@ constexpr int kCsrSlack = 64;     // a pass may run this many entries past its t
 constexpr bool kCsrLateGather = true;  // gather x while reducing rows (see csr_spmv_kernel)
 constexpr int kRowThreads = 256;  // row-per-subwarp kernel: work-group size
 constexpr int kRowU = 4;          // rows per subwarp in the row-per-subwarp kernel
-constexpr int kRowIters = 8;      // row groups per work-group in the row-per-subwarp kernel
-constexpr int kRowMaxRows = 65536;  // larger matrices take the load-balanced kernel
+constexpr int kRowMaxRows = 32768;  // larger matrices take the load-balanced kernel
 constexpr int64_t kStageMinNnz = 8192;  // staged-rows kernel: fewer entries take the load-balanced kernel
 
 inline int64_t csr_tiles(int64_t nnz) { return nnz > 0 ? ceil_div(nnz, kCsrTile) : 1; }
@@ -24,10 +23,10 @@ struct KState;
 // one partial per tile in dot_partials[epi][csr_tiles(nnz)] (fixed order).
 // With a solver state st, a set st->flag skips the work (the caller reduces
 // the partials with finish_kernel).
-// Subwarp width of the row-per-subwarp kernel for A, or 0 when A takes the
-// load-balanced kernel: A is small (at most kRowMaxRows rows) and its rows
-// are short and even (max_row_len known and at most twice the power of two
-// at or above the mean row length).
+// Subwarp width of the row-per-subwarp kernel for A, or 0 when A takes
+// another kernel: the staged-rows kernel does not take A, A is small (at most
+// kRowMaxRows rows) and its rows are short and even (max_row_len known and at
+// most twice the power of two at or above the mean row length).
 int csr_rows_sub(const spx_matrix &A);
 // Number of dot partials the CSR product with epi > 0 writes for A.
 int64_t csr_dot_parts(const spx_matrix &A);
