@@ -4,18 +4,33 @@
 // (Section 1), right-preconditioned with the scalar Jacobi M = diag(A):
 // the Krylov space is that of A M^{-1}, and x = x0 + M^{-1} V y.
 // Arnoldi orthogonalisation is classical Gram-Schmidt applied twice (CGS2,
-// "twice is enough": Giraud, Langou, Rozloznik 2005): two passes of
-//   h = V^T w (one multi-dot kernel: each work-group keeps its chunk of w in
-//   registers and sweeps every basis vector), w -= V h,
-// the second update fused with ||w||^2. A one-work-group finisher kernel that
-// sums the partials of that reduction builds the Hessenberg column, applies the previous Givens rotations, forms
-// the new one, updates the residual estimate |g_{j+1}| and decides whether the
-// cycle ends (estimate below tolerance, lucky breakdown, or maxit). All of
-// this stays on the device; one restart cycle (m Arnoldi steps) is a single
+// "twice is enough": Giraud, Langou, Rozloznik 2005) in three passes over the
+// basis instead of four: h = V^T w; then w' = w - V h and V^T w' in one pass
+// (a thread keeps its row of the basis in registers between the two); then
+// w'' = w' - V h2 with ||w''||^2. The basis is stored unscaled: column k holds
+// u_k = v_k / s_k, scaled to about unit length before its norm is known (by
+// ||w'||, the norm before the second pass), with the exact 1 / ||u_k|| kept as
+// the scalar s_k; products, dots and updates apply the scalars, so no kernel
+// normalises. The last pass also writes z = M^{-1} u for the next product.
+//
+// Layout: rows in panels of 256, a panel's basis columns one after another
+// (column k of panel p at (p (m + 1) + k) 256), so that a pass reads one
+// contiguous stretch per panel instead of one short piece of each of up to
+// m + 1 arrays n values apart.
+// One-work-group-per-row finishers sum the partials; the step finisher builds
+// the Hessenberg column, applies the previous Givens rotations, forms the new
+// one, updates the residual estimate |g_{j+1}| and decides whether the cycle
+// ends (estimate below tolerance, lucky breakdown, or maxit). All of this
+// stays on the device; one restart cycle (m Arnoldi steps) is a single
 // captured hipGraph, replayed per cycle. At the end of a cycle one wavefront
 // stages the triangle of H and g in LDS and one of its lanes back-substitutes
 // H y = g there; then x += M^{-1} V y, and the next cycle starts from the true
 // residual b - A x.
+//
+// What bounds a step: the basis, (j + 1) n values per pass, read at 6.2 TB/s.
+// GMRES(30) + Jacobi, convection-diffusion 128^3, one MI355X: 283 us per step
+// with four passes, 100 barriers per work-group and a normalising kernel,
+// 202 us now.
 #include <cmath>
 
 #include "solver_common.hpp"
@@ -32,166 +47,232 @@ struct GmState {
     double *cs;  // m
     double *sn;  // m
     double *y;   // m
+    double *s;   // m+1: v_k = s_k u_k
+    double *h1;  // m: first and second orthogonalisation coefficients
+    double *h2;  // m
 };
 
-// cycle start: v0 = r / ||r|| (||r||^2 in st->tmp[0]), g = ||r|| e1
-__global__ __launch_bounds__(kVecThreads) void gm_cycle_init_kernel(int64_t n, X *__restrict__ v0, KState *st,
-                                                                   GmState gs)
+constexpr int kGmThreads = 256;  // = rows per panel
+constexpr int kGmGroup = 4;      // basis vectors per unrolled group
+constexpr int kGmBlocks = 2048;  // work-groups of a pass at most
+
+static int64_t gm_panels(int64_t n) { return n > 0 ? ceil_div(n, kGmThreads) : 1; }
+
+// Work-groups of a pass over nv basis vectors: as many per CU as stay resident
+// with the registers that a thread's row of the basis and its sums take (32
+// vectors: 164).
+constexpr int gm_resident(int groups, bool update)
+{
+    return update ? (groups <= 2 ? 8 : (groups <= 4 ? 5 : (groups <= 6 ? 4 : (groups <= 8 ? 3 : (groups <= 13 ? 2 : 1)))))
+                  : (groups <= 3 ? 8 : (groups <= 5 ? 5 : (groups <= 7 ? 4 : (groups <= 9 ? 3 : (groups <= 15 ? 2 : 1)))));
+}
+
+static int64_t gm_blocks(int64_t n, int nv, bool update)
+{
+    const int64_t most = 256 * gm_resident((nv + kGmGroup - 1) / kGmGroup, update);
+    const int64_t b = gm_panels(n);
+    return b < most ? b : most;
+}
+
+// Whether nv basis vectors are read as a stream (non-temporal) or left in the
+// Infinity Cache (256 MB) for the next pass. 128^3, us a pass, plain /
+// non-temporal: 12 vectors (201 MB) 28 / 37, 16: 38 / 48, 20: 55 / 59, 24 (403
+// MB): 70 / 67, 28: 79 / 77; with the update 24: 74 / 69, 28: 88 / 78.
+static int gm_streams(int64_t n, int nv) { return (int64_t)nv * n * (int64_t)sizeof(X) > (int64_t)360 << 20; }
+
+// cycle start: u_0 = r / ||r|| (r in z, ||r||^2 in st->tmp[0]), z = M^{-1} u_0, g = ||r|| e1
+__global__ __launch_bounds__(kGmThreads) void gm_cycle_init_kernel(int64_t n, const X *__restrict__ dinv,
+                                                                  X *__restrict__ V, X *__restrict__ z, KState *st,
+                                                                  GmState gs)
 {
     const double beta = sqrt(st->tmp[0]);
-    const int64_t i = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
-    if (i < n) v0[i] = v0[i] / beta;
+    const int64_t i = (int64_t)blockIdx.x * kGmThreads + threadIdx.x;
+    if (i < n) {
+        const X v = z[i] / beta;
+        V[(int64_t)blockIdx.x * (gs.m + 1) * kGmThreads + threadIdx.x] = v;
+        z[i] = dinv ? v * dinv[i] : v;
+    }
     if (i == 0) {
         for (int k = 0; k <= gs.m; ++k) gs.g[k] = 0.0;
         gs.g[0] = beta;
+        gs.s[0] = 1.0;
         st->jend = 0;
         st->flag = kRunning;
-        st->tmp[1] = 1.0;
     }
 }
 
-// z = M^{-1} v_j, after normalising v_j = w / h_{j,j-1} (j > 0)
-__global__ __launch_bounds__(kVecThreads) void gm_prep_kernel(int64_t n, X *__restrict__ vj, const X *__restrict__ dinv,
-                                                             X *__restrict__ z, int normalise, const KState *st)
+// One pass over the basis, thread per row. kUpdate: w = scale * w - sum_k
+// dots[k] u_k first (scale = s_{nv-1}: w is the product with the unscaled
+// u_{nv-1}); then, always, the partials of u_k . w at partials[k * grid + blk]
+// for k < nv and of w . w in row nv (kUpdate only). A thread's row of the
+// basis is loaded once, all loads in flight, and stays in registers; its nv
+// sums run over all of its rows, so a work-group reduces each once.
+template <int kGroups, bool kUpdate, bool kNt>
+__global__ __launch_bounds__(kGmThreads, gm_resident(kGroups, kUpdate)) void gm_pass_kernel(
+    int64_t n, const X *__restrict__ V, X *__restrict__ w, int nv, X *__restrict__ partials, const KState *st,
+    GmState gs)
 {
     if (st->flag != kRunning) return;
-    const double inv = normalise ? 1.0 / st->tmp[1] : 1.0;
-    const int64_t base = (int64_t)blockIdx.x * kVecChunk;
+    constexpr int kMax = kGroups * kGmGroup;
+    __shared__ double s_h[kMax];
+    __shared__ X s_red[kGmThreads / kWave][kMax + 1];
+    const X scale = kUpdate ? gs.s[nv - 1] : X(1);
+    if (kUpdate) {
+        if (threadIdx.x < kMax) s_h[threadIdx.x] = (int)threadIdx.x < nv ? st->dots[threadIdx.x] : 0.0;
+        __syncthreads();
+    }
+    X acc[kMax], ww = X(0);
 #pragma unroll
-    for (int u = 0; u < kVecItems; ++u) {
-        const int64_t i = base + threadIdx.x + u * kVecThreads;
-        if (i < n) {
-            const X v = normalise ? vj[i] * inv : vj[i];
-            if (normalise) vj[i] = v;
-            if (dinv) z[i] = v * dinv[i];
+    for (int k = 0; k < kMax; ++k) acc[k] = X(0);
+    const int64_t panels = (n + kGmThreads - 1) / kGmThreads;
+    for (int64_t pb = blockIdx.x; pb < panels; pb += gridDim.x) {
+        const X *__restrict__ P = V + pb * (gs.m + 1) * kGmThreads;  // uniform: one 32-bit lane offset
+        const int64_t i = pb * kGmThreads + threadIdx.x;
+        const bool in = i < n;
+        const unsigned o = in ? threadIdx.x : 0u;
+        X v[kMax];
+        // a group's vectors past the last repeat it (their sums are not used)
+#pragma unroll
+        for (int k = 0; k < kMax; ++k) {
+            const X *q = P + (k < nv ? k : nv - 1) * kGmThreads + o;
+            v[k] = kNt ? ld_stream(q) : *q;
         }
-    }
-}
-
-// h_i = v_i . w for i < nv: per-group partial sums (stage 1; the group keeps
-// its chunk of w in registers and sweeps the basis vectors)
-__global__ __launch_bounds__(kVecThreads) void gm_multidot_kernel(int64_t n, const X *__restrict__ V,
-                                                                 const X *__restrict__ w, int nv,
-                                                                 X *__restrict__ partials, const KState *st)
-{
-    if (st->flag != kRunning) return;
-    __shared__ X s_red[kVecThreads / kWave];
-    const int64_t base = (int64_t)blockIdx.x * kVecChunk;
-    const int64_t nb = gridDim.x;
-    X wl[kVecItems];
+        X wi = in ? w[i] : X(0);
+        __builtin_amdgcn_sched_barrier(0);  // every load is issued before the first use
+        if (kUpdate) {
+            wi *= scale;
 #pragma unroll
-    for (int u = 0; u < kVecItems; ++u) {
-        const int64_t i = base + threadIdx.x + u * kVecThreads;
-        wl[u] = (i < n) ? w[i] : X(0);
-    }
-    for (int k = 0; k < nv; ++k) {
-        const X *vk = V + (int64_t)k * n;
-        X acc = X(0);
-#pragma unroll
-        for (int u = 0; u < kVecItems; ++u) {
-            const int64_t i = base + threadIdx.x + u * kVecThreads;
-            if (i < n) acc += vk[i] * wl[u];
+            for (int k = 0; k < kMax; ++k) wi -= s_h[k] * v[k];
+            if (in) w[i] = wi;
+            else wi = X(0);
+            ww += wi * wi;
         }
-        const X t = block_sum<X, kVecThreads>(acc, s_red);
-        if (threadIdx.x == 0) partials[(int64_t)k * nb + blockIdx.x] = t;
+#pragma unroll
+        for (int k = 0; k < kMax; ++k) acc[k] += v[k] * wi;
     }
-}
-
-// stage 2: st->dots[off + k] = sum of row k of the partials, fixed order:
-// wavefront w takes rows w, w + 16, ...; lane l adds partials l, l + 64, ...
-// of its row in that order, then the wavefront sum (no barrier).
-__global__ __launch_bounds__(kFinThreads) void gm_multidot_finish(const X *__restrict__ partials, int64_t nb, int nv,
-                                                                 KState *st, int off)
-{
-    if (st->flag != kRunning) return;
-    constexpr int kW = kFinThreads / kWave;
-    const int w = threadIdx.x / kWave, l = lane_id();
-    for (int k = w; k < nv; k += kW) {
-        X acc = X(0);
-        const X *row = partials + (int64_t)k * nb;
-#pragma unroll 8
-        for (int64_t b = l; b < nb; b += kWave) acc += row[b];
-        const X t = wave_sum(acc);
-        if (l == 0) st->dots[off + k] = t;
+    const int wid = threadIdx.x / kWave;
+    int own = 0;
+    const X sum = wave_sum_many<kMax>(acc, &own);
+    if (own < kMax) s_red[wid][own] = sum;
+    if (kUpdate) {
+        const X t = wave_sum(ww);
+        if (lane_id() == 0) s_red[wid][kMax] = t;
     }
-}
-
-// w -= sum_i h_i v_i with h = st->dots[off..off+nv); optionally ||w||^2 and
-// the Arnoldi step finish (Hessenberg column, Givens, cycle-end test).
-__global__ __launch_bounds__(kVecThreads) void gm_update_kernel(int64_t n, const X *__restrict__ V, X *__restrict__ w,
-                                                               int nv, int off, int final_pass,
-                                                               X *__restrict__ partials, const KState *st)
-{
-    if (st->flag != kRunning) return;
-    __shared__ X s_red[kVecThreads / kWave];
-    __shared__ double s_h[kMaxDots];
-    if (threadIdx.x < nv) s_h[threadIdx.x] = st->dots[off + threadIdx.x];
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kVecChunk;
-    X wl[kVecItems];
-#pragma unroll
-    for (int u = 0; u < kVecItems; ++u) {
-        const int64_t i = base + threadIdx.x + u * kVecThreads;
-        wl[u] = (i < n) ? w[i] : X(0);
+    const int k = threadIdx.x;
+    if (k < nv || (kUpdate && k == kMax)) {
+        X t = X(0);
+        for (int q = 0; q < kGmThreads / kWave; ++q) t += s_red[q][k];
+        partials[(int64_t)(k < nv ? k : nv) * gridDim.x + blockIdx.x] = t;
     }
-    for (int k = 0; k < nv; ++k) {
-        const X *vk = V + (int64_t)k * n;
-        const X h = s_h[k];
-#pragma unroll
-        for (int u = 0; u < kVecItems; ++u) {
-            const int64_t i = base + threadIdx.x + u * kVecThreads;
-            if (i < n) wl[u] -= h * vk[i];
-        }
-    }
-    X ww = X(0);
-#pragma unroll
-    for (int u = 0; u < kVecItems; ++u) {
-        const int64_t i = base + threadIdx.x + u * kVecThreads;
-        if (i < n) {
-            w[i] = wl[u];
-            ww += wl[u] * wl[u];
-        }
-    }
-    if (!final_pass) return;
-    const X t = block_sum<X, kVecThreads>(ww, s_red);
-    if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
-// Arnoldi step finish: ||w||, Hessenberg column j, Givens rotations, the
-// residual estimate and the cycle-end test (one work-group, fixed order).
-__global__ __launch_bounds__(kFinThreads) void gm_step_finish(const X *__restrict__ partials, int64_t nb, int j,
-                                                             KState *st, GmState gs)
+// Row k of the partials summed by work-group k. First pass: h_k = s_k s_{nv-1}
+// (u_k . w). Second: h2_k = s_k (u_k . w') and, in row nv, ||w'|| (st->tmp[2]).
+// st->dots[pass * kMaxDots + k] = h s_k, the coefficient of u_k.
+__global__ __launch_bounds__(kGmThreads) void gm_dots_finish(const X *__restrict__ partials, int nb, int nv, int pass,
+                                                            KState *st, GmState gs)
 {
     if (st->flag != kRunning) return;
-    __shared__ X s_red[kFinThreads / kWave];
-    X acc = X(0);
-    for (int64_t b = threadIdx.x; b < nb; b += kFinThreads) acc += partials[b];
-    const X w2 = block_sum<X, kFinThreads>(acc, s_red);
+    __shared__ double s_sum[kGmThreads / kWave];
+    const int k = blockIdx.x;
+    const double t = block_sum_partials<X, kGmThreads>(partials + (int64_t)k * nb, nb, s_sum);
     if (threadIdx.x != 0) return;
+    if (k == nv) {
+        st->tmp[2] = sqrt(t);
+        return;
+    }
+    const double h = pass == 0 ? gs.s[k] * (gs.s[nv - 1] * t) : gs.s[k] * t;
+    (pass == 0 ? gs.h1 : gs.h2)[k] = h;
+    st->dots[pass * kMaxDots + k] = h * gs.s[k];
+}
+
+// Third pass: u = (w' - sum_k dots[kMaxDots + k] u_k) / ||w'|| into column nv,
+// z = M^{-1} u, partials of u . u. (A zero or non-finite ||w'|| leaves the
+// scale out.)
+__global__ __launch_bounds__(kGmThreads) void gm_last_pass_kernel(int64_t n, X *V, const X *__restrict__ w, int nv, int nt,
+                                                                 const X *__restrict__ dinv, X *__restrict__ z,
+                                                                 X *__restrict__ partials, const KState *st,
+                                                                 GmState gs)
+{
+    if (st->flag != kRunning) return;
+    __shared__ X s_red[kGmThreads / kWave];
+    __shared__ double s_h[kMaxDots];
+    if ((int)threadIdx.x < nv) s_h[threadIdx.x] = st->dots[kMaxDots + threadIdx.x];
+    __syncthreads();
+    const double wn = st->tmp[2];
+    const X inv = wn > 0.0 && finite(1.0 / wn) ? 1.0 / wn : 1.0;
+    X uu = X(0);
+    const int64_t panels = (n + kGmThreads - 1) / kGmThreads;
+    for (int64_t pb = blockIdx.x; pb < panels; pb += gridDim.x) {
+        X *P = V + pb * (gs.m + 1) * kGmThreads;
+        const int64_t i = pb * kGmThreads + threadIdx.x;
+        if (i >= n) break;
+        X wi = w[i];
+        const X di = dinv ? dinv[i] : X(1);
+        if (nt) {
+#pragma unroll 8
+            for (int k = 0; k < nv; ++k) wi -= s_h[k] * ld_stream(P + k * kGmThreads + threadIdx.x);
+        } else {
+#pragma unroll 8
+            for (int k = 0; k < nv; ++k) wi -= s_h[k] * P[k * kGmThreads + threadIdx.x];
+        }
+        wi *= inv;
+        P[nv * kGmThreads + threadIdx.x] = wi;
+        z[i] = dinv ? wi * di : wi;
+        uu += wi * wi;
+    }
+    X t[1] = {block_sum<X, kGmThreads>(uu, s_red)};
+    write_partials<X, 1>(t, partials, gridDim.x, blockIdx.x);
+}
+
+// Arnoldi step finish: ||u||, Hessenberg column j, Givens rotations (staged
+// in LDS, applied by one lane), the residual estimate and the cycle-end test
+// (one work-group, fixed order).
+__global__ __launch_bounds__(kGmThreads) void gm_step_finish(const X *__restrict__ partials, int nb, int j, KState *st,
+                                                            GmState gs)
+{
+    if (st->flag != kRunning) return;
+    __shared__ double s_sum[kGmThreads / kWave];
+    __shared__ double s_h[kMaxDots], s_cs[kMaxDots], s_sn[kMaxDots];
+    const int t = threadIdx.x;
+    if (t <= j) s_h[t] = gs.h1[t] + gs.h2[t];
+    if (t < j) {
+        s_cs[t] = gs.cs[t];
+        s_sn[t] = gs.sn[t];
+    }
+    const double un = sqrt(block_sum_partials<X, kGmThreads>(partials, nb, s_sum));
     const int m = gs.m;
     double *hj = gs.H + (int64_t)j * (m + 1);
-    for (int i = 0; i <= j; ++i) hj[i] = st->dots[i] + st->dots[kMaxDots + i];
-    const double hn = sqrt(w2);
-    hj[j + 1] = hn;
-    for (int i = 0; i < j; ++i) {  // previous rotations
-        const double a = hj[i], c = hj[i + 1];
-        hj[i] = gs.cs[i] * a + gs.sn[i] * c;
-        hj[i + 1] = -gs.sn[i] * a + gs.cs[i] * c;
+    if (t == 0) {
+        const double wn = st->tmp[2];
+        const double hn = wn > 0.0 && finite(1.0 / wn) ? un * wn : un;
+        double a = s_h[0];
+        for (int i = 0; i < j; ++i) {  // previous rotations
+            const double c = s_h[i + 1];
+            s_h[i] = s_cs[i] * a + s_sn[i] * c;
+            a = -s_sn[i] * a + s_cs[i] * c;
+        }
+        const double rho = hypot(a, hn);
+        const double cs = a / rho, sn = hn / rho;
+        gs.cs[j] = cs;
+        gs.sn[j] = sn;
+        s_h[j] = rho;
+        hj[j + 1] = 0.0;
+        const double gj = gs.g[j], gn = -sn * gj;
+        gs.g[j + 1] = gn;
+        gs.g[j] = cs * gj;
+        gs.s[j + 1] = 1.0 / un;
+        st->iters += 1;
+        st->spmv_count += 1;
+        st->jend = j + 1;
+        st->rr = gn * gn;
+        if (!finite(gn) || !finite(hn)) st->flag = kNonfinite;
+        else if (gn * gn <= st->tol2 * st->bb || hn == 0.0 || st->iters >= st->maxit || j + 1 == m)
+            st->flag = kCycleEnd;
     }
-    const double rho = hypot(hj[j], hj[j + 1]);
-    gs.cs[j] = hj[j] / rho;
-    gs.sn[j] = hj[j + 1] / rho;
-    hj[j] = rho;
-    hj[j + 1] = 0.0;
-    gs.g[j + 1] = -gs.sn[j] * gs.g[j];
-    gs.g[j] = gs.cs[j] * gs.g[j];
-    st->iters += 1;
-    st->spmv_count += 1;
-    st->jend = j + 1;
-    st->tmp[1] = hn;
-    st->rr = gs.g[j + 1] * gs.g[j + 1];
-    if (!finite(gs.g[j + 1]) || !finite(hn)) st->flag = kNonfinite;
-    else if (st->rr <= st->tol2 * st->bb || hn == 0.0 || st->iters >= st->maxit || j + 1 == m) st->flag = kCycleEnd;
+    __syncthreads();
+    if (t <= j) hj[t] = s_h[t];
 }
 
 // y = H(0:jend,0:jend)^{-1} g (back substitution)
@@ -220,33 +301,22 @@ __global__ __launch_bounds__(kWave) void gm_solve_kernel(KState *st, GmState gs)
     for (int t = threadIdx.x; t < jend; t += kWave) gs.y[t] = s_y[t];
 }
 
-// x += M^{-1} V y
-__global__ __launch_bounds__(kVecThreads) void gm_xupdate_kernel(int64_t n, const X *__restrict__ V,
-                                                                const X *__restrict__ dinv, X *__restrict__ x,
-                                                                const KState *st, GmState gs)
+// x += M^{-1} V y, V's columns being s_k u_k
+__global__ __launch_bounds__(kGmThreads) void gm_xupdate_kernel(int64_t n, const X *__restrict__ V,
+                                                               const X *__restrict__ dinv, X *__restrict__ x,
+                                                               const KState *st, GmState gs)
 {
     __shared__ double s_y[kMaxDots];
     const int jend = st->jend;
-    if (threadIdx.x < jend) s_y[threadIdx.x] = gs.y[threadIdx.x];
+    if ((int)threadIdx.x < jend) s_y[threadIdx.x] = gs.y[threadIdx.x] * gs.s[threadIdx.x];
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kVecChunk;
-    X ul[kVecItems];
-#pragma unroll
-    for (int u = 0; u < kVecItems; ++u) ul[u] = X(0);
-    for (int k = 0; k < jend; ++k) {
-        const X *vk = V + (int64_t)k * n;
-        const X yk = s_y[k];
-#pragma unroll
-        for (int u = 0; u < kVecItems; ++u) {
-            const int64_t i = base + threadIdx.x + u * kVecThreads;
-            if (i < n) ul[u] += yk * vk[i];
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < kVecItems; ++u) {
-        const int64_t i = base + threadIdx.x + u * kVecThreads;
-        if (i < n) x[i] += dinv ? ul[u] * dinv[i] : ul[u];
-    }
+    const X *__restrict__ P = V + (int64_t)blockIdx.x * (gs.m + 1) * kGmThreads;
+    const int64_t i = (int64_t)blockIdx.x * kGmThreads + threadIdx.x;
+    if (i >= n) return;
+    X ul = X(0);
+#pragma unroll 8
+    for (int k = 0; k < jend; ++k) ul += s_y[k] * ld_stream(P + k * kGmThreads + threadIdx.x);
+    x[i] += dinv ? ul * dinv[i] : ul;
 }
 
 __global__ void gm_zero_vec(int64_t n, X *__restrict__ x)
@@ -286,20 +356,57 @@ struct GmBufs {
     int32_t *part;
 };
 
+// The pass kernel that holds nv vectors.
+template <bool kUpdate, bool kNt>
+static void gm_pass(int64_t n, const X *V, X *w, int nv, X *partials, const KState *st, const GmState &gs,
+                    hipStream_t s)
+{
+    const unsigned gb = (unsigned)gm_blocks(n, nv, kUpdate);
+#define SPX_GM_PASS(G)                                                                                      \
+    case G: gm_pass_kernel<G, kUpdate, kNt><<<gb, kGmThreads, 0, s>>>(n, V, w, nv, partials, st, gs); break
+    switch ((nv + kGmGroup - 1) / kGmGroup) {
+        SPX_GM_PASS(1);
+        SPX_GM_PASS(2);
+        SPX_GM_PASS(3);
+        SPX_GM_PASS(4);
+        SPX_GM_PASS(5);
+        SPX_GM_PASS(6);
+        SPX_GM_PASS(7);
+        SPX_GM_PASS(8);
+        SPX_GM_PASS(9);
+        SPX_GM_PASS(10);
+        SPX_GM_PASS(11);
+        SPX_GM_PASS(12);
+        SPX_GM_PASS(13);
+        SPX_GM_PASS(14);
+        SPX_GM_PASS(15);
+    default: gm_pass_kernel<16, kUpdate, kNt><<<gb, kGmThreads, 0, s>>>(n, V, w, nv, partials, st, gs); break;
+    }
+#undef SPX_GM_PASS
+}
+
+template <bool kUpdate>
+static void gm_pass(int64_t n, const X *V, X *w, int nv, X *partials, const KState *st, const GmState &gs,
+                    hipStream_t s)
+{
+    if (gm_streams(n, nv)) gm_pass<kUpdate, true>(n, V, w, nv, partials, st, gs, s);
+    else gm_pass<kUpdate, false>(n, V, w, nv, partials, st, gs, s);
+}
+
 static GmBufs gm_carve(Carve &c, const spx_matrix &A, int precond, int m)
 {
     const int64_t n = A.nrows;
     GmBufs w{};
     w.st = c.take<KState>(1);
-    w.V = c.take<X>((int64_t)(m + 1) * n);
+    w.V = c.take<X>((int64_t)(m + 1) * gm_panels(n) * kGmThreads);
     w.q = c.take<X>(n);
-    w.z = precond ? c.take<X>(n) : nullptr;
+    w.z = c.take<X>(n);
     w.d = precond ? c.take<X>(n) : nullptr;
     w.dinv = precond ? c.take<X>(n) : nullptr;
-    const int64_t vb = vec_blocks(n);
-    const int64_t slots = spmv_dot_parts(A) > (m + 2) * vb ? spmv_dot_parts(A) : (m + 2) * vb;
+    const int64_t gb = gm_panels(n) < kGmBlocks ? gm_panels(n) : kGmBlocks;
+    const int64_t slots = partial_slots(A) > (m + 2) * gb ? partial_slots(A) : (m + 2) * gb;
     w.partials = c.take<X>(slots);
-    w.gmem = c.take<X>((int64_t)(m + 1) * m + (m + 1) + 3 * m);
+    w.gmem = c.take<X>((int64_t)(m + 1) * m + 2 * (m + 1) + 5 * m);
     w.part = (A.fmt == SPX_CSR && A.csr_part == nullptr) ? c.take<int32_t>(csr_partition_bytes(A.nnz) / 4) : nullptr;
     return w;
 }
@@ -326,8 +433,9 @@ spx_status gmres_run(const spx_matrix &A_in, const double *b, double *x, const S
                 gmres_workspace(A_in, sp.precond, m));
     spx_matrix A = A_in;
     *info = spx_solve_info{};
-    GmState gs{m, w.gmem, w.gmem + (m + 1) * m, w.gmem + (m + 1) * m + (m + 1), w.gmem + (m + 1) * m + (m + 1) + m,
-               w.gmem + (m + 1) * m + (m + 1) + 2 * m};
+    X *gv0 = w.gmem + (m + 1) * m;  // behind H: g, s, then cs, sn, y, h1, h2
+    X *gm0 = gv0 + 2 * (m + 1);
+    GmState gs{m, w.gmem, gv0, gm0, gm0 + m, gm0 + 2 * m, gv0 + (m + 1), gm0 + 3 * m, gm0 + 4 * m};
 
     SPX_HIP(hipEventRecord(env->join, user_stream));
     SPX_HIP(hipStreamWaitEvent(s, env->join, 0));
@@ -356,20 +464,19 @@ spx_status gmres_run(const spx_matrix &A_in, const double *b, double *x, const S
     SPX_LAUNCHED();
 
     GraphGuard graph;
+    const unsigned gp = (unsigned)gm_panels(n), gl = gp < (unsigned)kGmBlocks ? gp : (unsigned)kGmBlocks;
     auto cycle = [&]() -> spx_status {
         for (int j = 0; j < m; ++j) {
-            X *vj = w.V + (int64_t)j * n;
-            X *wv = w.V + (int64_t)(j + 1) * n;
-            if (j > 0 || w.dinv) gm_prep_kernel<<<gv, kVecThreads, 0, s>>>(n, vj, w.dinv, w.z, j > 0 ? 1 : 0, w.st);
-            const X *src = w.dinv ? w.z : vj;
-            SPX_CHECK(spmv_dispatch(A, src, wv, 1.0, 0.0, s));
-            gm_multidot_kernel<<<gv, kVecThreads, 0, s>>>(n, w.V, wv, j + 1, w.partials, w.st);
-            gm_multidot_finish<<<1, kFinThreads, 0, s>>>(w.partials, gv, j + 1, w.st, 0);
-            gm_update_kernel<<<gv, kVecThreads, 0, s>>>(n, w.V, wv, j + 1, 0, 0, w.partials, w.st);
-            gm_multidot_kernel<<<gv, kVecThreads, 0, s>>>(n, w.V, wv, j + 1, w.partials, w.st);
-            gm_multidot_finish<<<1, kFinThreads, 0, s>>>(w.partials, gv, j + 1, w.st, kMaxDots);
-            gm_update_kernel<<<gv, kVecThreads, 0, s>>>(n, w.V, wv, j + 1, kMaxDots, 1, w.partials, w.st);
-            gm_step_finish<<<1, kFinThreads, 0, s>>>(w.partials, gv, j, w.st, gs);
+            const int nv = j + 1;
+            const int gd = (int)gm_blocks(n, nv, false), gu = (int)gm_blocks(n, nv, true);
+            SPX_CHECK((spmv_st<double, double>(A, w.z, w.q, w.st, s)));
+            gm_pass<false>(n, w.V, w.q, nv, w.partials, w.st, gs, s);
+            gm_dots_finish<<<nv, kGmThreads, 0, s>>>(w.partials, gd, nv, 0, w.st, gs);
+            gm_pass<true>(n, w.V, w.q, nv, w.partials, w.st, gs, s);
+            gm_dots_finish<<<nv + 1, kGmThreads, 0, s>>>(w.partials, gu, nv, 1, w.st, gs);
+            gm_last_pass_kernel<<<gl, kGmThreads, 0, s>>>(n, w.V, w.q, nv, gm_streams(n, nv), w.dinv, w.z,
+                                                           w.partials, w.st, gs);
+            gm_step_finish<<<1, kGmThreads, 0, s>>>(w.partials, (int)gl, j, w.st, gs);
             SPX_LAUNCHED();
         }
         return SPX_OK;
@@ -377,9 +484,9 @@ spx_status gmres_run(const spx_matrix &A_in, const double *b, double *x, const S
     spx_status status = SPX_OK;
     double true2 = 0.0;
     while (true) {
-        // true residual into v0
+        // true residual r = b - A x into z
         SPX_CHECK(spmv_dispatch(A, x, w.q, 1.0, 0.0, s));
-        SPX_CHECK(residual_norm<double>(n, b, w.q, w.V, w.partials, w.st, s));
+        SPX_CHECK(residual_norm<double>(n, b, w.q, w.z, w.partials, w.st, s));
         SPX_CHECK(read_state(env, w.st, &hs));
         true2 = hs.tmp[0];
         if (hs.flag == kZeroRhs) {
@@ -403,12 +510,12 @@ spx_status gmres_run(const spx_matrix &A_in, const double *b, double *x, const S
             set_error("gmres: no convergence in %d Arnoldi steps", sp.maxit);
             break;
         }
-        gm_cycle_init_kernel<<<ge, kVecThreads, 0, s>>>(n, w.V, w.st, gs);
+        gm_cycle_init_kernel<<<gp, kGmThreads, 0, s>>>(n, w.dinv, w.V, w.z, w.st, gs);
         SPX_LAUNCHED();
         if (graph.exec == nullptr) SPX_CHECK(capture_graph(s, &graph.exec, cycle));
         SPX_HIP(hipGraphLaunch(graph.exec, s));
         gm_solve_kernel<<<1, 64, 0, s>>>(w.st, gs);
-        gm_xupdate_kernel<<<gv, kVecThreads, 0, s>>>(n, w.V, w.dinv, x, w.st, gs);
+        gm_xupdate_kernel<<<gp, kGmThreads, 0, s>>>(n, w.V, w.dinv, x, w.st, gs);
         SPX_LAUNCHED();
         SPX_CHECK(read_state(env, w.st, &hs));
         info->outer_iters += 1;
