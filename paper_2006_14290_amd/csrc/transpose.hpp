@@ -1,5 +1,5 @@
-// transpose.hpp -- CSR transpose on the device (a stable radix sort of the
-// column indices; see transpose.hip).
+// transpose.hpp -- CSR transpose on the device (a stable sort of the entries
+// by column; see transpose.hip).
 #pragma once
 
 #include "common.hpp"
