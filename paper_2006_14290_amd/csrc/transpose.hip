@@ -2,7 +2,8 @@
 //
 // In CSR, A^T is A's entries ordered by (column, row). A's entries are
 // already in row order, so a stable sort of their column indices yields that
-// order. Up to 2^22 columns, two steps, most significant digit first:
+// order. Up to 2^22 columns and 30
+// million entries, two steps, most significant digit first:
 //   1. a stable partition of the entries (column, row, value) into at most
 //      2,048 buckets of consecutive columns: per tile of 4,096 entries a
 //      histogram of buckets, prefix sums over the tiles (coalesced: a thread
@@ -17,7 +18,7 @@
 //      into segments whose counts are summed in one kernel more, so one heavy
 //      column does not serialise the sort.
 // Values travel with their entries: nothing is gathered through a
-// permutation. More columns take the least-significant-digit radix sort
+// permutation. Larger matrices take the least-significant-digit radix sort
 // below: 8-bit digits, ceil(bits(ncols - 1) / 8) passes, carrying each entry's
 // position k in A:
 //   1. per tile of kRxTile entries, a 256-bin digit histogram, stored
@@ -210,14 +211,23 @@ struct TpShape {
     int64_t tiles;
 };
 
-// Buckets of 2^shift columns, at most 1,024 of them up to 2^21 columns (2,048
-// columns each), then 2,048. 0 buckets: more columns than the sort takes.
+// Buckets of 2^shift columns: of at most kTpFill entries on average, so that
+// few exceed a segment, and not fewer than 512 of them unless they would hold
+// less than 2,048 entries. 0 buckets: more columns or entries than the two
+// steps take.
+constexpr int64_t kTpFill = kTpSegment * 9 / 10;
+
 static TpShape tp_shape(int32_t ncols, int64_t nnz)
 {
     TpShape t{ncols, 0, 0, ceil_div(nnz, kTpTile)};
-    if (ncols > kTpMaxBuckets * kTpMaxWidth) return t;
-    const int most = ncols <= (1 << 21) ? 1024 : kTpMaxBuckets;
-    while (ceil_div(ncols, int64_t(1) << t.shift) > most) ++t.shift;
+    if (ncols > kTpMaxBuckets * kTpMaxWidth || nnz > kTpMaxBuckets * kTpFill) return t;
+    int64_t fill = nnz / 512;
+    fill = fill < 2048 ? 2048 : (fill > kTpFill ? kTpFill : fill);
+    int64_t want = ceil_div(nnz, fill);  // buckets
+    if (want > kTpMaxBuckets) want = kTpMaxBuckets;
+    // the widest buckets that are at least so many (or one column each)
+    while ((2 << t.shift) <= kTpMaxWidth && ceil_div(ncols, int64_t(2) << t.shift) >= want) ++t.shift;
+    while (ceil_div(ncols, int64_t(1) << t.shift) > kTpMaxBuckets) ++t.shift;
     t.buckets = (int32_t)ceil_div(ncols, int64_t(1) << t.shift);
     return t;
 }
@@ -267,6 +277,7 @@ __global__ __launch_bounds__(kTpThreads) void tp_hist_kernel(const int32_t *__re
         for (int it = 0; it < 8 && left != 0; ++it) {
             const int32_t k = readlane(key[j], __builtin_ctzll(left));
             const lane_mask_t m = ballot64(key[j] == k);
+            if (__popcll(m) < 4) break;  // scattered
             if (lane_id() == 0) atomicAdd(&h[k], __popcll(m));
             left &= ~m;
         }
@@ -404,12 +415,16 @@ __global__ __launch_bounds__(kTpThreads) void tp_partition_kernel(
 {
     extern __shared__ int32_t s_cnt[];  // [kTpWaves][buckets]
     __shared__ int32_t s_row[kTpWaves][kTpWaveTile];
+    // neighbouring tiles on one XCD: their entries of a bucket are neighbours
+    // in the output, and meet in its L2
+    const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
+    if (tile * kTpTile >= nnz) return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
     int32_t *cnt = s_cnt + w * buckets;
     for (int b = threadIdx.x; b < kTpWaves * buckets; b += kTpThreads) s_cnt[b] = 0;
     for (int i = lane; i < kTpWaveTile; i += kWave) s_row[w][i] = -1;
     __syncthreads();
-    const int64_t e0 = (int64_t)blockIdx.x * kTpTile + (int64_t)w * kTpWaveTile;
+    const int64_t e0 = tile * kTpTile + (int64_t)w * kTpWaveTile;
     const int64_t e1 = e0 + kTpWaveTile < nnz ? e0 + kTpWaveTile : nnz;
     uint32_t c[kTpItems];  // column, and above kTpColBits the place among the wavefront's entries of its bucket
 #pragma unroll
@@ -443,7 +458,7 @@ __global__ __launch_bounds__(kTpThreads) void tp_partition_kernel(
     }
     __syncthreads();
     for (int b = threadIdx.x; b < buckets; b += kTpThreads) {
-        int32_t run = offs[(int64_t)blockIdx.x * buckets + b];
+        int32_t run = offs[tile * buckets + b];
 #pragma unroll
         for (int q = 0; q < kTpWaves; ++q) {
             const int32_t t = s_cnt[q * buckets + b];
@@ -720,17 +735,20 @@ static spx_status tp_run(const spx_matrix &A, spx_matrix &At, const TpShape &t, 
     int bits = 0;
     while ((1 << bits) < t.buckets) ++bits;
     tp_hist_kernel<<<(unsigned)t.tiles, kTpThreads, 0, stream>>>(A.colidx, nnz, t.ncols, t.shift, t.buckets, b.hist);
-    tp_group_sums<<<(unsigned)groups, kTpScanThreads, 0, stream>>>(b.hist, t.tiles, per, t.buckets, b.gsum);
+    int32_t *gsum = per > 1 ? b.gsum : b.hist;  // groups of one tile: their sums are its counts
+    if (per > 1)
+        tp_group_sums<<<(unsigned)groups, kTpScanThreads, 0, stream>>>(b.hist, t.tiles, per, t.buckets, gsum);
     if (t.buckets <= kTpScanThreads)
-        tp_bucket_scan<1><<<1, kTpScanThreads, 0, stream>>>(b.gsum, (int)groups, t.buckets, b.bstart, b.segstart,
+        tp_bucket_scan<1><<<1, kTpScanThreads, 0, stream>>>(gsum, (int)groups, t.buckets, b.bstart, b.segstart,
                                                             b.multistart);
     else
-        tp_bucket_scan<2><<<1, kTpScanThreads, 0, stream>>>(b.gsum, (int)groups, t.buckets, b.bstart, b.segstart,
+        tp_bucket_scan<2><<<1, kTpScanThreads, 0, stream>>>(gsum, (int)groups, t.buckets, b.bstart, b.segstart,
                                                             b.multistart);
-    tp_tile_offsets<<<(unsigned)groups, kTpScanThreads, 0, stream>>>(b.hist, t.tiles, per, t.buckets, b.gsum);
+    if (per > 1)
+        tp_tile_offsets<<<(unsigned)groups, kTpScanThreads, 0, stream>>>(b.hist, t.tiles, per, t.buckets, gsum);
     const size_t lds_p = (size_t)kTpWaves * t.buckets * 4, lds_b = (size_t)kTpWaves * ((size_t)4 << t.shift);
     const size_t lds_s = (size_t)kTpSortWaves * ((size_t)2 << t.shift);
-    tp_partition_kernel<T><<<(unsigned)t.tiles, kTpThreads, lds_p, stream>>>(
+    tp_partition_kernel<T><<<(unsigned)pad_to_xcds(t.tiles), kTpThreads, lds_p, stream>>>(
         A.rowptr, A.nrows, A.colidx, val, nnz, t.ncols, t.shift, bits, t.buckets, b.hist, b.col, b.row, bval);
     SPX_LAUNCHED();
     const unsigned segs = (unsigned)(t.buckets + nnz / kTpSegment);
