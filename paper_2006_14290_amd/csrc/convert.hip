@@ -9,10 +9,11 @@
 //               whole wavefront (coalesced stores).
 //  COO -> CSR   rowptr from the sorted row array: entry p writes rowptr[i] = p
 //               for every row i in (row[p-1], row[p]] (one pass, coalesced).
-//  CSR -> ELL   one lane per row writes its K slots (slot-major, coalesced).
+//  CSR -> ELL   and SELL-P: 64 rows per work-group through LDS, lane per row.
 //  CSR -> HYB   first K entries of a row -> ELL slots; the rest -> COO part at
 //               an offset from an exclusive scan of max(0, len - K).
-//  ELL -> CSR   per-row counts of stored slots, scan, then a copy in slot order.
+//  ELL -> CSR   and SELL-P: per-row counts of stored slots, scan, then a copy in
+//               slot order through LDS.
 //  HYB -> CSR   ELL counts plus COO counts (from the COO row pointer), scan,
 //               then a per-row merge of the two ascending lists.
 #include <vector>
@@ -25,8 +26,10 @@
 namespace spx {
 
 constexpr int kCvThreads = 256;
-constexpr int kCvStageRows = 128;   // rows per work-group of the staged conversions
-constexpr int kCvStageNnz = 4096;   // their LDS capacity in entries
+constexpr int kCvStageRows = kWave;  // rows per work-group of the staged conversions, one per lane
+constexpr int kCvStageNnz = 2560;    // their LDS capacity in entries
+constexpr int kCvParts = kCvThreads / kWave;  // wavefronts: each takes a part of every row's slots
+constexpr int kCvChunk = 8;          // slots in flight per lane
 constexpr int kScanItems = 4;                           // per thread
 constexpr int kScanBlock = kCvThreads * kScanItems;     // elements per scan block
 
@@ -245,12 +248,16 @@ __global__ __launch_bounds__(kCvThreads) void coo_rowptr_kernel(const int32_t *_
         for (int32_t i = r + 1; i <= n; ++i) rowptr[i] = (int32_t)nnz;
 }
 
-// ------------------------------------------------------------------ CSR -> ELL / HYB (ELL part)
-// Conversions that turn rows into slot columns (or back) go through LDS:
-// the kCvStageRows consecutive rows of a work-group occupy one contiguous
-// stretch of the CSR arrays, read (or written) coalesced there, while each
-// thread walks its own row in LDS. A block whose rows hold more than
-// kCvStageNnz entries reads / writes the CSR arrays directly instead.
+// ------------------------------------------------------------------ CSR <-> slot columns
+// Conversions that turn rows into slot columns (ELL, SELL-P) or back go
+// through LDS: the 64 consecutive rows of a work-group occupy one contiguous
+// stretch of the CSR arrays, read (or written) coalesced there, while lane l
+// of every wavefront holds row l and the four wavefronts share the slots. A
+// block whose rows hold more than kCvStageNnz entries reads / writes the CSR
+// arrays directly instead. What bounds it: the copy; the split keeps 20
+// wavefronts per CU at it (30 KB of LDS per work-group). 27-point 100^3,
+// float64, one MI355X: CSR to ELL 300 -> 123 us, ELL to CSR 326 -> 111 us
+// against 128 rows in two wavefronts and 48 KB, each thread walking its row.
 struct StageRange {
     int32_t base, cnt;
     bool staged;
@@ -272,9 +279,25 @@ template <typename V>
 __device__ __forceinline__ void stage_in(const int32_t *__restrict__ col, const V *__restrict__ val,
                                          const StageRange &g, int32_t *s_col, V *s_val)
 {
-    for (int32_t j = threadIdx.x; j < g.cnt; j += kCvStageRows) {
-        s_col[j] = col[g.base + j];
-        s_val[j] = val[g.base + j];
+    constexpr int kIt = kCvStageNnz / kCvThreads;
+    static_assert(kCvStageNnz % kCvThreads == 0, "whole steps");
+    int32_t c[kIt];
+    V v[kIt];
+#pragma unroll
+    for (int u = 0; u < kIt; ++u) {
+        const int32_t j = threadIdx.x + u * kCvThreads;
+        if (j < g.cnt) {
+            c[u] = ld_stream(col + g.base + j);
+            v[u] = ld_stream(val + g.base + j);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kIt; ++u) {
+        const int32_t j = threadIdx.x + u * kCvThreads;
+        if (j < g.cnt) {
+            s_col[j] = c[u];
+            s_val[j] = v[u];
+        }
     }
     __syncthreads();
 }
@@ -284,37 +307,64 @@ __device__ __forceinline__ void stage_out(int32_t *__restrict__ col, V *__restri
                                           const int32_t *s_col, const V *s_val)
 {
     __syncthreads();
-    for (int32_t j = threadIdx.x; j < g.cnt; j += kCvStageRows) {
+#pragma unroll 5
+    for (int32_t j = threadIdx.x; j < g.cnt; j += kCvThreads) {
         col[g.base + j] = s_col[j];
         val[g.base + j] = s_val[j];
     }
 }
 
+// Where row i's slots lie: slot k at base + k * step, `width` of them.
+struct SlotRow {
+    int64_t base, step;
+    int32_t width;
+};
+
+// ELL (sets == nullptr): K columns of ld rows. SELL-P: slices of C = 1 <<
+// log2c rows, the widths' prefix sums in sets.
+struct SlotLayout {
+    int32_t K;
+    int64_t ld;
+    const int32_t *sets;
+    int32_t log2c;
+    __device__ __forceinline__ SlotRow row(int64_t i) const
+    {
+        if (sets == nullptr) return SlotRow{i, ld, K};
+        const int64_t s = i >> log2c, l = i & ((1 << log2c) - 1);
+        const int32_t k0 = sets[s];
+        return SlotRow{((int64_t)k0 << log2c) + l, int64_t(1) << log2c, sets[s + 1] - k0};
+    }
+};
+
+// rows: those of the slot arrays (ELL: ld, SELL-P: whole slices).
 template <typename V>
-__global__ __launch_bounds__(kCvStageRows) void csr_to_ell_kernel(const int32_t *__restrict__ rowptr,
+__global__ __launch_bounds__(kCvThreads) void csr_to_slots_kernel(const int32_t *__restrict__ rowptr,
                                                                  const int32_t *__restrict__ col,
-                                                                 const V *__restrict__ val, int32_t n, int32_t K,
-                                                                 int64_t ld, int32_t *__restrict__ ecol,
+                                                                 const V *__restrict__ val, int32_t n, int64_t rows,
+                                                                 SlotLayout lay, int32_t *__restrict__ ecol,
                                                                  V *__restrict__ eval)
 {
     __shared__ int32_t s_col[kCvStageNnz];
     __shared__ V s_val[kCvStageNnz];
     const int64_t r0 = (int64_t)blockIdx.x * kCvStageRows;
-    const int64_t i = r0 + threadIdx.x;
+    const int64_t i = r0 + lane_id();
     const StageRange g = stage_range(rowptr, n, r0);
     if (g.staged) stage_in(col, val, g, s_col, s_val);
-    if (i >= ld) return;
+    if (i >= rows) return;
     const int32_t a = (i < n) ? rowptr[i] : 0;
     const int32_t len = (i < n) ? rowptr[i + 1] - a : 0;
-    for (int32_t k = 0; k < K; ++k) {
-        const int64_t q = (int64_t)k * ld + i;
+    const SlotRow sr = lay.row(i);
+#pragma unroll 4
+    for (int32_t k = threadIdx.x / kWave; k < sr.width; k += kCvParts) {
+        const int64_t q = sr.base + k * sr.step;
+        int32_t c = -1;
+        V v = V(0);
         if (k < len) {
-            ecol[q] = g.staged ? s_col[a - g.base + k] : col[a + k];
-            eval[q] = g.staged ? s_val[a - g.base + k] : val[a + k];
-        } else {
-            ecol[q] = -1;
-            eval[q] = V(0);
+            c = g.staged ? s_col[a - g.base + k] : col[a + k];
+            v = g.staged ? s_val[a - g.base + k] : val[a + k];
         }
+        ecol[q] = c;
+        eval[q] = v;
     }
 }
 
@@ -365,34 +415,66 @@ __global__ __launch_bounds__(kCvThreads) void hyb_coo_kernel(const int32_t *__re
     }
 }
 
-// ------------------------------------------------------------------ ELL -> CSR and HYB -> CSR
-// rowptr[i+1] = stored ELL slots of row i (+ COO entries of row i if coo_rp)
-__global__ __launch_bounds__(kCvThreads) void ell_count_kernel(const int32_t *__restrict__ ecol, int32_t n,
-                                                              int32_t K, int64_t ld,
-                                                              const int32_t *__restrict__ coo_rp,
-                                                              int32_t *__restrict__ rowptr)
+// ------------------------------------------------------------------ slot columns -> CSR
+// rowptr[i+1] = stored slots of row i (+ COO entries of row i if coo_rp)
+__global__ __launch_bounds__(kCvThreads) void slots_count_kernel(const int32_t *__restrict__ ecol, int32_t n,
+                                                                SlotLayout lay, const int32_t *__restrict__ coo_rp,
+                                                                int32_t *__restrict__ rowptr)
 {
     const int64_t i = (int64_t)blockIdx.x * kCvThreads + threadIdx.x;
     if (i == 0) rowptr[0] = 0;
     if (i >= n) return;
+    const SlotRow sr = lay.row(i);
     int32_t c = 0;
-    for (int32_t k = 0; k < K; ++k) c += ecol[(int64_t)k * ld + i] >= 0;
+#pragma unroll 8
+    for (int32_t k = 0; k < sr.width; ++k) c += ld_stream(ecol + sr.base + k * sr.step) >= 0;
     if (coo_rp) c += coo_rp[i + 1] - coo_rp[i];
     rowptr[i + 1] = c;
 }
 
-// Row i of the CSR result: the row's ELL entries (slot order, padding
-// dropped) merged with its COO entries (if any), ascending by column.
+// *total += stored slots of all rows. At most kTotalBlocks work-groups: every
+// one adds to the same word, about 15 ns each (3,907 of them: 58 us).
+constexpr int kTotalBlocks = 512;
+constexpr int kTotalThreads = 1024;
+__global__ __launch_bounds__(kTotalThreads) void slots_total_kernel(const int32_t *__restrict__ ecol, int32_t n,
+                                                                SlotLayout lay, unsigned long long *__restrict__ total)
+{
+    __shared__ unsigned long long s_sum[kTotalThreads / kWave];
+    unsigned long long sum = 0;
+    for (int64_t i = (int64_t)blockIdx.x * kTotalThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kTotalThreads) {
+        const SlotRow sr = lay.row(i);
+        int32_t c = 0;
+#pragma unroll 8
+        for (int32_t k = 0; k < sr.width; ++k) c += ld_stream(ecol + sr.base + k * sr.step) >= 0;
+        sum += (unsigned long long)c;
+    }
+    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    if (lane_id() == 0) s_sum[threadIdx.x / kWave] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long t = 0;
+        for (int w = 0; w < kTotalThreads / kWave; ++w) t += s_sum[w];
+        if (t) atomicAdd(total, t);
+    }
+}
+
+// Row i of the CSR result: the row's slots (slot order, padding dropped)
+// merged with its COO entries (if any), ascending by column. Wavefront w
+// counts and then places its part of the 64 rows' slots; COO entries that all
+// come after the slots (the canonical split) are copied row by row, others
+// are merged by one lane.
 template <typename V>
-__global__ __launch_bounds__(kCvStageRows) void ell_hyb_to_csr_kernel(
-    const int32_t *__restrict__ ecol, const V *__restrict__ eval, int32_t n, int32_t K, int64_t ld,
+__global__ __launch_bounds__(kCvThreads) void slots_to_csr_kernel(
+    const int32_t *__restrict__ ecol, const V *__restrict__ eval, int32_t n, SlotLayout lay,
     const int32_t *__restrict__ coo_rp, const int32_t *__restrict__ ccol, const V *__restrict__ cval,
     const int32_t *__restrict__ rowptr, int32_t *__restrict__ col, V *__restrict__ val)
 {
     __shared__ int32_t s_col[kCvStageNnz];
     __shared__ V s_val[kCvStageNnz];
+    __shared__ int32_t s_cnt[kCvParts][kWave], s_last[kCvParts][kWave];
     const int64_t r0 = (int64_t)blockIdx.x * kCvStageRows;
-    const int64_t i = r0 + threadIdx.x;
+    const int lane = lane_id(), part = threadIdx.x / kWave;
+    const int64_t i = r0 + lane;
     const StageRange g = stage_range(rowptr, n, r0);
     // entry o of the CSR result goes to LDS slot o - base when staged
     auto put = [&](int32_t o, int32_t c, V v) {
@@ -404,21 +486,81 @@ __global__ __launch_bounds__(kCvStageRows) void ell_hyb_to_csr_kernel(
             val[o] = v;
         }
     };
-    if (i < n) {
-        int32_t o = rowptr[i];
-        int32_t cb = coo_rp ? coo_rp[i] : 0;
-        const int32_t ce = coo_rp ? coo_rp[i + 1] : 0;
-        for (int32_t k = 0; k < K; ++k) {
-            const int64_t q = (int64_t)k * ld + i;
-            const int32_t c = ecol[q];
-            if (c < 0) continue;
-            while (cb < ce && ccol[cb] < c) {  // COO entries with a smaller column come first
-                put(o++, ccol[cb], cval[cb]);
-                ++cb;
-            }
-            put(o++, c, eval[q]);
+    SlotRow sr{0, 0, 0};
+    if (i < n) sr = lay.row(i);
+    const int32_t per = (sr.width + kCvParts - 1) / kCvParts;
+    const int32_t k0 = part * per < sr.width ? part * per : sr.width;
+    const int32_t k1 = k0 + per < sr.width ? k0 + per : sr.width;
+    // the first kCvChunk slots of the part stay in registers for the placing
+    int32_t c[kCvChunk];
+    V v[kCvChunk];
+    int32_t cnt = 0, last = -1;
+#pragma unroll
+    for (int u = 0; u < kCvChunk; ++u) {
+        c[u] = -1;
+        if (k0 + u < k1) {
+            c[u] = ld_stream(ecol + sr.base + (k0 + u) * sr.step);
+            v[u] = ld_stream(eval + sr.base + (k0 + u) * sr.step);
         }
-        for (; cb < ce; ++cb) put(o++, ccol[cb], cval[cb]);
+    }
+#pragma unroll
+    for (int u = 0; u < kCvChunk; ++u)
+        if (c[u] >= 0) {
+            ++cnt;
+            last = c[u];
+        }
+#pragma unroll 8
+    for (int32_t k = k0 + kCvChunk; k < k1; ++k) {
+        const int32_t t = ecol[sr.base + k * sr.step];
+        if (t >= 0) {
+            ++cnt;
+            last = t;
+        }
+    }
+    s_cnt[part][lane] = cnt;
+    s_last[part][lane] = last;
+    __syncthreads();
+    const int32_t cb = coo_rp && i < n ? coo_rp[i] : 0, ce = coo_rp && i < n ? coo_rp[i + 1] : 0;
+    int32_t o = i < n ? rowptr[i] : 0, ell_end = o, ell_last = -1;
+    for (int q = 0; q < kCvParts; ++q) {
+        if (q < part) o += s_cnt[q][lane];
+        ell_end += s_cnt[q][lane];
+        ell_last = s_last[q][lane] >= 0 ? s_last[q][lane] : ell_last;
+    }
+    const bool after = cb >= ce || ccol[cb] > ell_last;  // no COO entry before a slot
+    if (after) {
+#pragma unroll
+        for (int u = 0; u < kCvChunk; ++u)
+            if (c[u] >= 0) put(o++, c[u], v[u]);
+        for (int32_t k = k0 + kCvChunk; k < k1; ++k) {
+            const int64_t q = sr.base + k * sr.step;
+            const int32_t t = ecol[q];
+            if (t >= 0) put(o++, t, eval[q]);
+        }
+    } else if (part == 0) {
+        int32_t p = cb;
+        for (int32_t k = 0; k < sr.width; ++k) {
+            const int64_t q = sr.base + k * sr.step;
+            const int32_t t = ecol[q];
+            if (t < 0) continue;
+            while (p < ce && ccol[p] < t) {  // COO entries with a smaller column come first
+                put(o++, ccol[p], cval[p]);
+                ++p;
+            }
+            put(o++, t, eval[q]);
+        }
+        for (; p < ce; ++p) put(o++, ccol[p], cval[p]);
+    }
+    if (coo_rp) {
+        // the rows whose COO entries follow their slots, a wavefront to each
+        lane_mask_t m = ballot64(after && cb < ce);
+        for (int t = 0; m != 0; ++t) {
+            const int src = __builtin_ctzll(m);
+            m &= m - 1;
+            if (t % kCvParts != part) continue;
+            const int32_t b = readlane(cb, src), e = readlane(ce, src), to = readlane(ell_end, src);
+            for (int32_t p = b + lane; p < e; p += kWave) put(to + (p - b), ccol[p], cval[p]);
+        }
     }
     if (g.staged) stage_out(col, val, g, s_col, s_val);
 }
@@ -509,85 +651,6 @@ __global__ __launch_bounds__(kCvThreads) void sellp_width_kernel(const int32_t *
     if (out64) out64[s] = w;
 }
 
-// One thread per (slice, lane): row s*C + l written slot by slot (lanes of a
-// slice are adjacent, so each slot column is written coalesced).
-template <typename V>
-__global__ __launch_bounds__(kCvStageRows) void csr_to_sellp_kernel(const int32_t *__restrict__ rowptr,
-                                                                   const int32_t *__restrict__ col,
-                                                                   const V *__restrict__ val, int32_t n, int32_t C,
-                                                                   int64_t nslices, const int32_t *__restrict__ sets,
-                                                                   int32_t *__restrict__ scol, V *__restrict__ sval)
-{
-    __shared__ int32_t s_col[kCvStageNnz];
-    __shared__ V s_val[kCvStageNnz];
-    const int64_t r0 = (int64_t)blockIdx.x * kCvStageRows;
-    const int64_t r = r0 + threadIdx.x;  // = slice * C + lane
-    const StageRange g = stage_range(rowptr, n, r0);
-    if (g.staged) stage_in(col, val, g, s_col, s_val);
-    if (r >= nslices * C) return;
-    const int64_t s = r / C, l = r % C;
-    const int32_t a = (r < n) ? rowptr[r] : 0;
-    const int32_t len = (r < n) ? rowptr[r + 1] - a : 0;
-    const int32_t k0 = sets[s], w = sets[s + 1] - k0;
-    for (int32_t k = 0; k < w; ++k) {
-        const int64_t q = ((int64_t)k0 + k) * C + l;
-        if (k < len) {
-            scol[q] = g.staged ? s_col[a - g.base + k] : col[a + k];
-            sval[q] = g.staged ? s_val[a - g.base + k] : val[a + k];
-        } else {
-            scol[q] = -1;
-            sval[q] = V(0);
-        }
-    }
-}
-
-__global__ __launch_bounds__(kCvThreads) void sellp_count_kernel(const int32_t *__restrict__ sets,
-                                                                const int32_t *__restrict__ scol, int32_t n,
-                                                                int32_t C, int32_t *__restrict__ rowptr)
-{
-    const int64_t r = (int64_t)blockIdx.x * kCvThreads + threadIdx.x;
-    if (r == 0) rowptr[0] = 0;
-    if (r >= n) return;
-    const int64_t s = r / C, l = r % C;
-    const int32_t k0 = sets[s], w = sets[s + 1] - k0;
-    int32_t c = 0;
-    for (int32_t k = 0; k < w; ++k) c += scol[((int64_t)k0 + k) * C + l] >= 0;
-    rowptr[r + 1] = c;
-}
-
-template <typename V>
-__global__ __launch_bounds__(kCvStageRows) void sellp_to_csr_kernel(const int32_t *__restrict__ sets,
-                                                                   const int32_t *__restrict__ scol,
-                                                                   const V *__restrict__ sval, int32_t n, int32_t C,
-                                                                   const int32_t *__restrict__ rowptr,
-                                                                   int32_t *__restrict__ col, V *__restrict__ val)
-{
-    __shared__ int32_t s_col[kCvStageNnz];
-    __shared__ V s_val[kCvStageNnz];
-    const int64_t r0 = (int64_t)blockIdx.x * kCvStageRows;
-    const int64_t r = r0 + threadIdx.x;
-    const StageRange g = stage_range(rowptr, n, r0);
-    if (r < n) {
-        const int64_t s = r / C, l = r % C;
-        const int32_t k0 = sets[s], w = sets[s + 1] - k0;
-        int32_t o = rowptr[r];
-        for (int32_t k = 0; k < w; ++k) {
-            const int64_t q = ((int64_t)k0 + k) * C + l;
-            if (scol[q] >= 0) {
-                if (g.staged) {
-                    s_col[o - g.base] = scol[q];
-                    s_val[o - g.base] = sval[q];
-                } else {
-                    col[o] = scol[q];
-                    val[o] = sval[q];
-                }
-                ++o;
-            }
-        }
-    }
-    if (g.staged) stage_out(col, val, g, s_col, s_val);
-}
-
 // ------------------------------------------------------------------ host side
 static size_t val_size(int32_t t) { return t == SPX_F64 ? 8 : (t == SPX_F32 ? 4 : 2); }
 
@@ -619,6 +682,33 @@ spx_status csr_max_row_len(const spx_matrix &A, int32_t *out, hipStream_t stream
         SPX_LAUNCHED();
     }
     return read_scalar(dm, out, stream);
+}
+
+static SlotLayout slot_layout(const spx_matrix &A)
+{
+    if (A.fmt != SPX_SELLP) return SlotLayout{A.ell_width, A.ell_ld, nullptr, 0};
+    int32_t log2c = 0;
+    while ((1 << log2c) < A.slice_size) ++log2c;
+    return SlotLayout{0, 0, A.slice_sets, log2c};
+}
+
+// Stored slots (padding not counted) of an ELL, HYB (ELL part) or SELL-P matrix.
+static spx_status slots_total(const spx_matrix &A, int64_t *out, hipStream_t stream)
+{
+    *out = 0;
+    if (A.nrows == 0) return SPX_OK;
+    DevScratch d;
+    SPX_HIP(hipMalloc(&d.p, sizeof(unsigned long long)));
+    auto *total = static_cast<unsigned long long *>(d.p);
+    SPX_CHECK(fill<unsigned long long>(total, 1, 0ull, stream));
+    const int64_t blocks = ceil_div(A.nrows, kTotalThreads);
+    slots_total_kernel<<<(unsigned)(blocks < kTotalBlocks ? blocks : kTotalBlocks), kTotalThreads, 0, stream>>>(
+        A.ell_col, A.nrows, slot_layout(A), total);
+    SPX_LAUNCHED();
+    unsigned long long h = 0;
+    SPX_CHECK(read_scalar(total, &h, stream));
+    *out = (int64_t)h;
+    return SPX_OK;
 }
 
 // Automatic HYB width: argmin over K of n*K*(sv+si) + sum max(0, len-K)*(sv+2si),
@@ -715,27 +805,8 @@ spx_status convert_plan(const spx_matrix &src, int32_t dst_fmt, int32_t ell_widt
         d.ell_ld = ell_ld > 0 ? ell_ld : n;
         SPX_REQUIRE(d.ell_ld >= n, SPX_ERR_ARG, "convert: ell_ld < nrows");
     } else if ((src.fmt == SPX_ELL || src.fmt == SPX_HYB) && dst_fmt == SPX_CSR) {
-        // count the stored entries on the device (padding dropped)
-        DevScratch s;
-        SPX_HIP(hipMalloc(&s.p, (size_t)(n + 1) * 8 + (size_t)scan_ws_bytes(n)));
-        int32_t *crp = static_cast<int32_t *>(s.p);
-        int32_t *cnt = crp + (n + 1);
-        int32_t tot = 0;
-        if (n > 0) {
-            const int32_t *coo_rp = nullptr;
-            if (src.fmt == SPX_HYB && src.coo_nnz > 0) {
-                coo_rowptr_kernel<<<(unsigned)ceil_div(src.coo_nnz, kCvThreads), kCvThreads, 0, stream>>>(
-                    src.rowidx, src.coo_nnz, src.nrows, crp);
-                SPX_LAUNCHED();
-                coo_rp = crp;
-            }
-            ell_count_kernel<<<(unsigned)ceil_div(n, kCvThreads), kCvThreads, 0, stream>>>(
-                src.ell_col, src.nrows, src.ell_width, src.ell_ld, coo_rp, cnt);
-            SPX_LAUNCHED();
-            SPX_CHECK(inclusive_scan<int32_t>(cnt + 1, n, static_cast<char *>(s.p) + (size_t)(n + 1) * 8, stream));
-            SPX_CHECK(read_scalar(cnt + n, &tot, stream));
-        }
-        d.nnz = tot;
+        SPX_CHECK(slots_total(src, &d.nnz, stream));
+        if (src.fmt == SPX_HYB) d.nnz += src.coo_nnz;
     } else if (src.fmt == SPX_CSR && dst_fmt == SPX_SELLP) {
         const int32_t C = sellp_c(dst->slice_size), T = sellp_t(dst->stride_factor);
         SPX_REQUIRE(C <= 256 && (C & (C - 1)) == 0, SPX_ERR_ARG, "convert: slice_size %d is not a power of two <= 256",
@@ -759,18 +830,7 @@ spx_status convert_plan(const spx_matrix &src, int32_t dst_fmt, int32_t ell_widt
         d.stride_factor = T;
         d.slice_cols = tot;
     } else if (src.fmt == SPX_SELLP && dst_fmt == SPX_CSR) {
-        DevScratch s;
-        SPX_HIP(hipMalloc(&s.p, (size_t)(n + 1) * 4 + (size_t)scan_ws_bytes(n)));
-        int32_t *cnt = static_cast<int32_t *>(s.p);
-        int32_t tot = 0;
-        if (n > 0) {
-            sellp_count_kernel<<<(unsigned)ceil_div(n, kCvThreads), kCvThreads, 0, stream>>>(
-                src.slice_sets, src.ell_col, src.nrows, src.slice_size, cnt);
-            SPX_LAUNCHED();
-            SPX_CHECK(inclusive_scan<int32_t>(cnt + 1, n, static_cast<char *>(s.p) + (size_t)(n + 1) * 4, stream));
-            SPX_CHECK(read_scalar(cnt + n, &tot, stream));
-        }
-        d.nnz = tot;
+        SPX_CHECK(slots_total(src, &d.nnz, stream));
     } else if (src.fmt == dst_fmt) {
         SPX_REQUIRE(false, SPX_ERR_ARG, "convert: source and destination formats are the same");
     } else {
@@ -809,8 +869,8 @@ static spx_status convert_typed(const spx_matrix &src, spx_matrix &dst, void *ws
     }
     if (src.fmt == SPX_CSR && (dst.fmt == SPX_ELL || dst.fmt == SPX_HYB)) {
         if (dst.ell_width > 0 && dst.ell_ld > 0) {
-            csr_to_ell_kernel<V><<<(unsigned)ceil_div(dst.ell_ld, kCvStageRows), kCvStageRows, 0, stream>>>(
-                src.rowptr, src.colidx, static_cast<const V *>(src.vals), n, dst.ell_width, dst.ell_ld, dst.ell_col,
+            csr_to_slots_kernel<V><<<(unsigned)ceil_div(dst.ell_ld, kCvStageRows), kCvThreads, 0, stream>>>(
+                src.rowptr, src.colidx, static_cast<const V *>(src.vals), n, dst.ell_ld, slot_layout(dst), dst.ell_col,
                 static_cast<V *>(dst.ell_val));
             SPX_LAUNCHED();
         }
@@ -837,11 +897,11 @@ static spx_status convert_typed(const spx_matrix &src, spx_matrix &dst, void *ws
             coo_rp = crp;
         }
         void *scan_ws = static_cast<char *>(ws) + (size_t)(n + 1) * 8;
-        ell_count_kernel<<<gr, kCvThreads, 0, stream>>>(src.ell_col, n, src.ell_width, src.ell_ld, coo_rp, dst.rowptr);
+        slots_count_kernel<<<gr, kCvThreads, 0, stream>>>(src.ell_col, n, slot_layout(src), coo_rp, dst.rowptr);
         SPX_LAUNCHED();
         SPX_CHECK(inclusive_scan<int32_t>(dst.rowptr + 1, n, scan_ws, stream));
-        ell_hyb_to_csr_kernel<V><<<(unsigned)ceil_div(n, kCvStageRows), kCvStageRows, 0, stream>>>(
-            src.ell_col, static_cast<const V *>(src.ell_val), n, src.ell_width, src.ell_ld, coo_rp, src.colidx,
+        slots_to_csr_kernel<V><<<(unsigned)ceil_div(n, kCvStageRows), kCvThreads, 0, stream>>>(
+            src.ell_col, static_cast<const V *>(src.ell_val), n, slot_layout(src), coo_rp, src.colidx,
             static_cast<const V *>(src.vals), dst.rowptr, dst.colidx, static_cast<V *>(dst.vals));
         SPX_LAUNCHED();
         return SPX_OK;
@@ -854,8 +914,8 @@ static spx_status convert_typed(const spx_matrix &src, spx_matrix &dst, void *ws
         SPX_LAUNCHED();
         if (ns > 0) {
             SPX_CHECK(inclusive_scan<int32_t>(dst.slice_sets + 1, ns, ws, stream));
-            csr_to_sellp_kernel<V><<<(unsigned)ceil_div(ns * C, kCvStageRows), kCvStageRows, 0, stream>>>(
-                src.rowptr, src.colidx, static_cast<const V *>(src.vals), n, C, ns, dst.slice_sets, dst.ell_col,
+            csr_to_slots_kernel<V><<<(unsigned)ceil_div(ns * C, kCvStageRows), kCvThreads, 0, stream>>>(
+                src.rowptr, src.colidx, static_cast<const V *>(src.vals), n, ns * C, slot_layout(dst), dst.ell_col,
                 static_cast<V *>(dst.ell_val));
             SPX_LAUNCHED();
         }
@@ -863,11 +923,11 @@ static spx_status convert_typed(const spx_matrix &src, spx_matrix &dst, void *ws
     }
     if (src.fmt == SPX_SELLP && dst.fmt == SPX_CSR) {
         if (n == 0) return fill<int32_t>(dst.rowptr, 1, 0, stream);
-        sellp_count_kernel<<<gr, kCvThreads, 0, stream>>>(src.slice_sets, src.ell_col, n, src.slice_size, dst.rowptr);
+        slots_count_kernel<<<gr, kCvThreads, 0, stream>>>(src.ell_col, n, slot_layout(src), nullptr, dst.rowptr);
         SPX_LAUNCHED();
         SPX_CHECK(inclusive_scan<int32_t>(dst.rowptr + 1, n, ws, stream));
-        sellp_to_csr_kernel<V><<<(unsigned)ceil_div(n, kCvStageRows), kCvStageRows, 0, stream>>>(
-            src.slice_sets, src.ell_col, static_cast<const V *>(src.ell_val), n, src.slice_size, dst.rowptr,
+        slots_to_csr_kernel<V><<<(unsigned)ceil_div(n, kCvStageRows), kCvThreads, 0, stream>>>(
+            src.ell_col, static_cast<const V *>(src.ell_val), n, slot_layout(src), nullptr, nullptr, nullptr, dst.rowptr,
             dst.colidx, static_cast<V *>(dst.vals));
         SPX_LAUNCHED();
         return SPX_OK;
