@@ -80,7 +80,8 @@ enum WideMode : int32_t {
 
 // Written by the host when the system is admitted. The product phase runs
 // the load-balanced CSR tile kernel over the system's ntiles tiles (its
-// partition in csr_part), one or two partials per tile in part_a (rows of
+// partition in csr_part) or, when its rows are short and even, as many
+// row blocks of the staged form, two partials per tile in part_a (rows of
 // ntiles); the vector phase works on nvb blocks of kWideRows rows, one or
 // two partials each, into one half of part while it reads the other half
 // (the halves alternate; each half holds two rows of nvb).
@@ -109,7 +110,8 @@ struct WideState {
     double alpha;                       // the last step length
     int32_t restart;  // CG: 1 = the next step restarts the recurrences (p = r, s = w)
     int32_t truer;    // r.r about to be summed is of r = b (2), of a true residual (1), recursive (0)
-    int32_t phase;    // which half of part the next vector phase reads
+    int16_t phase;    // which half of part the next vector phase reads
+    int16_t stage;    // the product: 0 = tiles; 1 + log2 of the lanes per row = staged rows
     int32_t bphase;   // BiCGSTAB: which part of a step the next product + vector pair runs
     double rho0, omega;  // BiCGSTAB: the previous r_hat.r, the last omega
 };

@@ -9,7 +9,8 @@
 // One iteration is two grid-wide phases over every listed system (a launch
 // boundary is the only global synchronisation):
 //   A  w = A r (or w = A x in the true-residual mode), partial sums of r.w:
-//      the load-balanced CSR tile kernel over every listed system's tiles;
+//      the load-balanced CSR tile kernel over every listed system's tiles, or
+//      its staged-rows form where the system's rows are short and even;
 //   V  gamma = r.r and delta = r.w from the partials; beta = gamma / gamma_old,
 //      alpha = gamma / (delta - beta gamma / alpha_old) (beta = 0 and
 //      alpha = gamma / delta when the recurrences start); p = r + beta p,
@@ -34,12 +35,26 @@
 // arithmetic is therefore independent of the other systems in the launch.
 #include "batch_cg.hpp"
 #include "spmv_csr.hpp"
+#include "spmv_csr_stage.hpp"
 #include "spmv_csr_tile.hpp"
 #include "wave.hpp"
 
 namespace spx {
 
 constexpr int kWideWaves = kWideThreads / kWave;
+constexpr int kWideStageWaves = kCsrThreads / kWave;
+constexpr int kWideStageCap = 512;   // entries a wavefront stages at once
+constexpr int kWideStageForms = 5;   // rows of up to 8, 16, 32, 64, 128 entries
+constexpr int kWideRunTiles = 16;    // consecutive tiles on one XCD
+static_assert(kWideThreads == kCsrThreads, "both phases reduce with the same work-group");
+
+// 16 bytes per lane into LDS; see lds_copy16. Temporal: the solved systems'
+// matrices are read again every iteration and may stay in the Infinity Cache.
+__device__ __forceinline__ void wide_copy16(const void *g, void *lds)
+{
+    __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) const void *)g,
+                                     (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
+}
 
 // Work-group sum in a fixed order (result in every thread).
 __device__ __forceinline__ double wide_wg_sum(double v, double *s_red)
@@ -64,24 +79,179 @@ __device__ __forceinline__ double wide_part_sum(const double *part, int32_t cnt,
     return wide_wg_sum(t, s_red);
 }
 
-// Product phase: one work-group per virtual tile (system, tile). The tile
-// kernel runs with its dot epilogue in both modes (w.r in the run mode; the
+// Row-length test of the staged product, spread over the blocks of the init
+// phase: the longest row of rows [r0, r1) (result in thread 0).
+__device__ double wide_longest_row(const WideSlot &S, int32_t r0, int32_t r1, double *s_red)
+{
+    int32_t m = 0;
+    for (int32_t i = r0 + threadIdx.x; i < r1; i += kWideThreads) m = max(m, S.rowptr[i + 1] - S.rowptr[i]);
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d /= 2) m = max(m, __shfl_xor(m, d));
+    __syncthreads();
+    if (lane_id() == 0) s_red[threadIdx.x / kWave] = (double)m;
+    __syncthreads();
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWideWaves; ++w) t = fmax(t, s_red[w]);
+    return t;
+}
+
+// Product form of a system from its blocks' longest rows: the rule of the
+// single product's staged-rows kernel. len is the power of two at or above
+// the longest row; rows fill at least half of len on average, so that the
+// ceil(n * len / 4096) row blocks are never more than the ntiles tiles.
+// Returns 1 + log2(len / 8), or 0 for the tile form.
+__device__ int16_t wide_stage_form(const WideSlot &S, const double *longest, double *s_red)
+{
+    double m = 0.0;
+    for (int32_t i = threadIdx.x; i < S.nvb; i += kWideThreads) m = fmax(m, longest[i]);
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d /= 2) m = fmax(m, __shfl_xor(m, d));
+    __syncthreads();
+    if (lane_id() == 0) s_red[threadIdx.x / kWave] = m;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWideWaves; ++w) m = fmax(m, s_red[w]);
+    if (S.nnz < kStageMinNnz || S.nnz > INT32_MAX - kStageMinNnz) return 0;
+    if (((reinterpret_cast<uintptr_t>(S.col) | reinterpret_cast<uintptr_t>(S.val)) & 15) != 0) return 0;
+    for (int f = 0; f < kWideStageForms; ++f) {
+        const int64_t len = 8 << f;
+        if (m <= (double)len) return 2 * S.nnz >= len * S.n ? (int16_t)(f + 1) : (int16_t)0;
+    }
+    return 0;
+}
+
+// Staged-rows form of one virtual tile (see csr_stage_kernel): rows
+// [k * 512 >> sh, + 512 >> sh) with 1 << sh lanes per row, each wavefront two
+// blocks of 64 >> sh rows, the second one copied into LDS while the first
+// one's gathers are in flight. Tiles past the last row write zero partials.
+__device__ __forceinline__ void wide_stage_tile(unsigned char *s_raw, double *s_red, int32_t k, const WideSlot &S,
+                                                int sh, const double *src, double *y, const double *dw)
+{
+    constexpr int kCap = kWideStageCap, kLen = 8;
+    const int lane = lane_id();
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    double *s_val = reinterpret_cast<double *>(s_raw + (size_t)wid * kCap * (sizeof(double) + sizeof(int32_t)));
+    int32_t *s_col = reinterpret_cast<int32_t *>(s_val + kCap);
+    const int g = lane >> sh, sl = lane & ((1 << sh) - 1);
+    const int32_t per = kWave >> sh;  // rows per block
+    const int32_t n = S.n;
+    const int32_t nnz8 = (int32_t)(S.nnz & ~(int64_t)7);
+    const int32_t first = (k * kWideStageWaves + wid) * 2 * per;  // below 2^31: k < ntiles
+    __syncthreads();  // LDS of a previous tile handled by this work-group is consumed
+    double d1 = 0.0, d2 = 0.0;
+    if (first < n) {
+        int32_t ra[2], rb[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int32_t r = first + t * per + g;
+            ra[t] = S.rowptr[r < n ? r : n];
+            rb[t] = S.rowptr[r + 1 < n ? r + 1 : n];
+        }
+        double wv[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int32_t r = first + t * per + g;
+            wv[t] = sl == 0 && r < n ? dw[r] : 0.0;
+        }
+        auto stage = [&](int32_t s, int32_t e) {
+            const int32_t a0 = s & ~3;
+            const int32_t lim = e < nnz8 ? e : nnz8;
+            const int32_t last = lim > 0 ? lim - 1 : 0;
+            const int32_t lastc = last & ~3, lastv = last & ~1;
+#pragma unroll
+            for (int u = 0; u < kCap / (4 * kWave); ++u) {
+                const int32_t p = a0 + (u * kWave + lane) * 4;
+                wide_copy16(S.col + (p < lastc ? p : lastc), s_col + u * kWave * 4);
+            }
+#pragma unroll
+            for (int u = 0; u < kCap / (2 * kWave); ++u) {
+                const int32_t p = a0 + (u * kWave + lane) * 2;
+                wide_copy16(S.val + (p < lastv ? p : lastv), s_val + u * kWave * 2);
+            }
+        };
+        stage(__builtin_amdgcn_readfirstlane(ra[0]), readlane(rb[0], kWave - 1));
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the copies have landed
+            const int32_t a0 = __builtin_amdgcn_readfirstlane(ra[t]) & ~3;
+            const int32_t lim = nnz8 - a0 > kCap ? a0 + kCap : nnz8;  // staged: [a0, lim)
+            const int32_t pe = rb[t] < lim ? rb[t] : lim;
+            int32_t c[kLen];
+            double v[kLen], xv[kLen];
+#pragma unroll
+            for (int u = 0; u < kLen; ++u) {
+                const int32_t p = ra[t] + sl + (u << sh);
+                const int32_t q = p < pe ? p - a0 : 0;
+                c[u] = s_col[q];
+                v[u] = s_val[q];
+                if (p >= pe) c[u] = 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kLen; ++u) xv[u] = src[c[u]];
+            if (t == 0) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this block's LDS reads are done
+                stage(__builtin_amdgcn_readfirstlane(ra[1]), readlane(rb[1], kWave - 1));
+            }
+            double sum = 0.0;
+#pragma unroll
+            for (int u = 0; u < kLen; ++u) {
+                const double f = sum + v[u] * xv[u];
+                sum = ra[t] + sl + (u << sh) < pe ? f : sum;
+            }
+            // the row's entries past the stage
+            for (int32_t p = ra[t] + sl; p < rb[t]; p += 1 << sh)
+                if (p >= lim) sum += S.val[p] * src[S.col[p]];
+            sum = subwave_sum_dyn(sum, 1 << sh);
+            const int32_t r = first + t * per + g;
+            if (sl == 0 && r < n) {
+                y[r] = sum;
+                d1 += sum * wv[t];
+                d2 += sum * sum;
+            }
+        }
+    }
+    d1 = block_sum<double, kCsrThreads>(d1, s_red);
+    d2 = block_sum<double, kCsrThreads>(d2, s_red);
+    const double v[2] = {d1, d2};
+    write_partials<double, 2>(v, S.part_a, S.ntiles, k);
+}
+
+// Product phase: one work-group per virtual tile (system, tile). Both forms
+// run with their dot epilogue in both modes (w.r in the run mode; the
 // true-residual mode multiplies x and ignores the partial).
-__global__ __launch_bounds__(kCsrThreads) void wide_a_kernel(const WideSlot *__restrict__ slots,
+// What bounds it: the matrix stream, out of the Infinity Cache once the
+// systems' matrices and vectors fit there. Measured on one MI355X, 16 Poisson
+// grids of 1.9 million rows together (143 MB per product): tile form 48 us,
+// staged form 29.6 us (4.8 TB/s); non-temporal copies, which the single
+// product uses, 39. Six work-groups per CU against five: 29.6 / 30.4 us.
+// Runs of 4, 16 and 64 tiles per XCD: 29.4 / 30.4 / 32.8 us (at five). 17
+// random columns per row (1.7 million rows) take the tile form: 185 us.
+__global__ __launch_bounds__(kCsrThreads, 6) void wide_a_kernel(const WideSlot *__restrict__ slots,
                                                              const WideState *__restrict__ st,
                                                              const WideMap *__restrict__ map,
                                                              const int32_t *__restrict__ ta_slot,
                                                              const int32_t *__restrict__ ta_local)
 {
+    constexpr size_t kTileLds = csr_tile_lds<double, double, kCsrTile, kCsrLateGather>();
+    constexpr size_t kStageLds = (size_t)kWideStageWaves * kWideStageCap * (sizeof(double) + sizeof(int32_t));
+    __shared__ __align__(16) unsigned char s_raw[kTileLds > kStageLds ? kTileLds : kStageLds];
+    __shared__ double s_red[kWideWaves];
     const int32_t total = map->total_ta;
-    for (int32_t v = blockIdx.x; v < total; v += gridDim.x) {
+    // XCD j takes runs of kWideRunTiles consecutive tiles: neighbouring rows share
+    // its L2, and every XCD has its share of every large system
+    constexpr int32_t kGroup = kWideRunTiles * kXcds;
+    const int32_t padded = (total + kGroup - 1) / kGroup * kGroup;
+    for (int32_t i = blockIdx.x; i < padded; i += gridDim.x) {
+        const int32_t w = i % kGroup;
+        const int32_t v = i - w + (w % kXcds) * kWideRunTiles + w / kXcds;
+        if (v >= total) continue;
         const int32_t s = ta_slot[v], k = ta_local[v];
         const int32_t mode = st[s].mode;
         if (mode != kWideRun && mode != kWideCheck) continue;
         const WideSlot S = slots[s];
-        // one instantiation of the tile kernel for every case (its LDS
-        // staging sets the occupancy); the second partial (y.y) is used by
-        // BiCGSTAB's t = A s only
+        // one instantiation of each form for every case; the second partial
+        // (y.y) is used by BiCGSTAB's t = A s only
         const double *src = mode == kWideRun ? S.r : S.x;
         const double *dw = src;
         double *y = S.w;
@@ -96,8 +266,12 @@ __global__ __launch_bounds__(kCsrThreads) void wide_a_kernel(const WideSlot *__r
                 continue;  // no product in this pair
             }
         }
-        csr_tile<double, double, 2, kCsrThreads, kCsrTile, 1, kCsrLateGather>(
-            k, S.n, S.nnz, S.ntiles, S.rowptr, S.col, S.val, src, y, 1.0, 0.0, dw, S.part_a, S.csr_part);
+        const int form = st[s].stage;
+        if (form > 0)
+            wide_stage_tile(s_raw, s_red, k, S, form - 1, src, y, dw);
+        else
+            csr_tile<double, double, 2, kCsrThreads, kCsrTile, 1, kCsrLateGather>(
+                s_raw, k, S.n, S.nnz, S.ntiles, S.rowptr, S.col, S.val, src, y, 1.0, 0.0, dw, S.part_a, S.csr_part);
     }
 }
 
@@ -162,6 +336,8 @@ __device__ void bicgstab_vector_phase(const WideSlot &S, const WideState &W0, bo
             S.rh[i] = bi;
             t0 += bi * bi;
         }
+        const double longest = wide_longest_row(S, r0, r1, s_red);
+        if (threadIdx.x == 0) part_out[S.nvb + lv] = longest;
         nw = 1;
         W.mode = kWideRun;
         W.bphase = 3;
@@ -181,6 +357,7 @@ __device__ void bicgstab_vector_phase(const WideSlot &S, const WideState &W0, bo
     } else if (W0.bphase == 3) {  // a true residual's r.r: converged, or (re)start
         const double tr = wide_part_sum(part_in, S.nvb, s_red);
         if (W0.truer == 2) W.bb = tr;
+        if (W0.truer == 2 && lead) W.stage = wide_stage_form(S, part_in + S.nvb, s_red);
         W.rr = tr;
         if (!__builtin_isfinite(tr)) {
             done(kSlotNonfinite);
@@ -281,10 +458,12 @@ __device__ void bicgstab_vector_phase(const WideSlot &S, const WideState &W0, bo
     if (lead && threadIdx.x == 0) *next = W;
 }
 
-// Vector phase and commit. Every block reads this iteration's state from st;
-// the first virtual block of each system writes the updated state to
-// st_next (the two buffers alternate from one iteration to the next).
-__global__ __launch_bounds__(kWideThreads) void wide_v_kernel(const WideSlot *__restrict__ slots,
+// Vector phase and commit; bound by its nine vector streams. The rows of a
+// block are loaded before the sums that scale them are formed: 1.9 million
+// rows 26.9 -> 24.3 us (5.7 TB/s). Every block reads this iteration's state
+// from st; the first virtual block of each system writes the updated state
+// to st_next (the two buffers alternate from one iteration to the next).
+__global__ __launch_bounds__(kWideThreads, 6) void wide_v_kernel(const WideSlot *__restrict__ slots,
                                                               const WideState *__restrict__ st,
                                                               WideState *__restrict__ st_next,
                                                               const WideMap *__restrict__ map,
@@ -313,29 +492,40 @@ __global__ __launch_bounds__(kWideThreads) void wide_v_kernel(const WideSlot *__
         bool wrote = false;  // this block stored a partial into part_out
         double t = 0.0;
         if (W0.mode == kWideRun) {
+            // the block's vectors do not wait for the sums that scale them
+            constexpr int kPer = kWideRows / kWideThreads;
+            double rv[kPer], wv[kPer], pv[kPer], sv[kPer], xv[kPer];
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int32_t i = r0 + u * kWideThreads + threadIdx.x;
+                rv[u] = wv[u] = pv[u] = sv[u] = xv[u] = 0.0;
+                if (i < r1) {
+                    rv[u] = S.r[i];
+                    wv[u] = S.w[i];
+                    xv[u] = S.x[i];
+                    if (!W0.restart) {
+                        pv[u] = S.p[i];
+                        sv[u] = S.s[i];
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
             const double gamma = wide_part_sum(part_in, S.nvb, s_red);
             const double delta = wide_part_sum(S.part_a, S.ntiles, s_red);
+            if (W0.truer == 2 && lead) W.stage = wide_stage_form(S, part_in + S.nvb, s_red);
             double alpha = 0.0, beta = 0.0;
             const int32_t step = run_decision(W, S, gamma, delta, alpha, beta);
             if (step == kStepTake) {
-                if (W0.restart) {
-                    for (int32_t i = r0 + threadIdx.x; i < r1; i += kWideThreads) {
-                        const double pi = S.r[i], si = S.w[i];
+#pragma unroll
+                for (int u = 0; u < kPer; ++u) {
+                    const int32_t i = r0 + u * kWideThreads + threadIdx.x;
+                    if (i < r1) {
+                        const double pi = W0.restart ? rv[u] : rv[u] + beta * pv[u];
+                        const double si = W0.restart ? wv[u] : wv[u] + beta * sv[u];
                         S.p[i] = pi;
                         S.s[i] = si;
-                        S.x[i] += alpha * pi;
-                        const double ri = S.r[i] - alpha * si;
-                        S.r[i] = ri;
-                        t += ri * ri;
-                    }
-                } else {
-                    for (int32_t i = r0 + threadIdx.x; i < r1; i += kWideThreads) {
-                        const double pi = S.r[i] + beta * S.p[i];
-                        const double si = S.w[i] + beta * S.s[i];
-                        S.p[i] = pi;
-                        S.s[i] = si;
-                        S.x[i] += alpha * pi;
-                        const double ri = S.r[i] - alpha * si;
+                        S.x[i] = xv[u] + alpha * pi;
+                        const double ri = rv[u] - alpha * si;
                         S.r[i] = ri;
                         t += ri * ri;
                     }
@@ -369,6 +559,8 @@ __global__ __launch_bounds__(kWideThreads) void wide_v_kernel(const WideSlot *__
                 S.r[i] = bi;
                 t += bi * bi;
             }
+            const double longest = wide_longest_row(S, r0, r1, s_red);
+            if (threadIdx.x == 0) part_out[S.nvb + lv] = longest;
             wrote = true;
             W.mode = kWideRun;
             W.restart = 1;

@@ -51,6 +51,9 @@ constexpr int kBackfill = 8;
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 constexpr int kWideIters = 8;                    // wide iterations per graph launch
+// Fewest iterations of a wide tick under a fixed count per tick: at 10 us or
+// more each, a tick's synchronisation and read-back (about 25 us) stay below 3 %.
+constexpr int kWideFixedIters = 96;
 constexpr int kWideGrids[3] = {256, 1024, 4096};  // physical grids of the wide graphs
 // the state alternates between two buffers; an even count ends in the first
 static_assert(kWideIters % 2 == 0, "wide iterations per graph must be even");
@@ -662,7 +665,12 @@ void worker_main(spx_server *Sp)
             if (hipEventElapsedTime(&ms, S.ev_w0, S.ev_w1) == hipSuccess && ms > 0.f) {
                 const double tick_ms = (S.cfg.tick_us > 0 ? S.cfg.tick_us : 2000) * 1e-3;
                 const double per = ms / S.wide_launches;
-                S.wide_launches = (int)std::max(1.0, std::min(64.0, tick_ms / per));
+                // a fixed iteration count bounds the wide ticks too, but not
+                // below kWideFixedIters
+                const double most = S.cfg.iters_per_tick > 0
+                                        ? std::max(S.cfg.iters_per_tick, kWideFixedIters) / kWideIters
+                                        : 64.0;
+                S.wide_launches = (int)std::max(1.0, std::min(std::min(64.0, most), tick_ms / per));
             }
         }
         {
@@ -1051,7 +1059,6 @@ spx_status cg_batch_run(spx_batch_system *sys, int32_t count, const BatchLayout 
     std::vector<WideSlot> whost;
     std::vector<WideState> wstate;
     std::vector<int32_t> vb((size_t)(2 * L.total_vb)), ta((size_t)(2 * L.total_ta)), widx((size_t)count, -1);
-    int64_t tot = 0, tta = 0;
     int32_t maxit_max = 1;
     for (int32_t i = 0; i < count; ++i) {
         const size_t vb_bytes = align256((size_t)sys[i].n * 8);
@@ -1099,18 +1106,7 @@ spx_status cg_batch_run(spx_batch_system *sys, int32_t count, const BatchLayout 
             w.nvb = wide_nvb(sys[i].n);
             w.maxit = maxit;
             w.tol2 = sys[i].tol * sys[i].tol;
-            const int32_t k = (int32_t)whost.size();
-            widx[i] = k;
-            for (int32_t v = 0; v < w.nvb; ++v) {
-                vb[tot + v] = k;
-                vb[L.total_vb + tot + v] = v;
-            }
-            tot += w.nvb;
-            for (int32_t v = 0; v < w.ntiles; ++v) {
-                ta[tta + v] = k;
-                ta[L.total_ta + tta + v] = v;
-            }
-            tta += w.ntiles;
+            widx[i] = (int32_t)whost.size();
             whost.push_back(w);
             WideState s0{};
             s0.mode = kWideInit;
@@ -1143,13 +1139,35 @@ spx_status cg_batch_run(spx_batch_system *sys, int32_t count, const BatchLayout 
         SPX_HIP(hipMemcpyAsync(host.data(), slots_dev, sizeof(BatchSlot) * (size_t)count, hipMemcpyDeviceToHost, stream));
     }
     if (L.nwide > 0) {
-        const WideMap m{(int32_t)L.total_vb, (int32_t)L.nwide, (int32_t)L.total_ta, 0};
         SPX_HIP(hipMemcpyAsync(wslots_dev, whost.data(), sizeof(WideSlot) * whost.size(), hipMemcpyHostToDevice, stream));
         SPX_HIP(hipMemcpyAsync(wstate_dev, wstate.data(), sizeof(WideState) * wstate.size(), hipMemcpyHostToDevice, stream));
-        SPX_HIP(hipMemcpyAsync(wmap_dev, &m, sizeof(m), hipMemcpyHostToDevice, stream));
-        SPX_HIP(hipMemcpyAsync(vb_dev, vb.data(), sizeof(int32_t) * vb.size(), hipMemcpyHostToDevice, stream));
-        SPX_HIP(hipMemcpyAsync(ta_dev, ta.data(), sizeof(int32_t) * ta.size(), hipMemcpyHostToDevice, stream));
-        const int grid = (int)std::min<int64_t>(std::max(L.total_vb, L.total_ta), 4096);
+        WideMap m{};
+        int grid = 0;
+        // Lists the blocks and tiles of the systems still running. Work-groups
+        // pass over a finished system's tiles one by one (a dependent load
+        // each), so the list is made anew whenever systems have finished.
+        auto list = [&]() -> spx_status {
+            int32_t tot = 0, tta = 0, nlisted = 0;
+            for (int32_t k = 0; k < (int32_t)whost.size(); ++k) {
+                if (wstate[k].mode == kWideDone) continue;
+                ++nlisted;
+                for (int32_t v = 0; v < whost[k].nvb; ++v, ++tot) {
+                    vb[tot] = k;
+                    vb[L.total_vb + tot] = v;
+                }
+                for (int32_t v = 0; v < whost[k].ntiles; ++v, ++tta) {
+                    ta[tta] = k;
+                    ta[L.total_ta + tta] = v;
+                }
+            }
+            m = WideMap{tot, nlisted, tta, 0};
+            grid = (int)std::min<int64_t>(std::max(tot, tta), 4096);
+            SPX_HIP(hipMemcpyAsync(wmap_dev, &m, sizeof(m), hipMemcpyHostToDevice, stream));
+            SPX_HIP(hipMemcpyAsync(vb_dev, vb.data(), sizeof(int32_t) * vb.size(), hipMemcpyHostToDevice, stream));
+            SPX_HIP(hipMemcpyAsync(ta_dev, ta.data(), sizeof(int32_t) * ta.size(), hipMemcpyHostToDevice, stream));
+            return SPX_OK;
+        };
+        SPX_CHECK(list());
         // an iteration either takes a CG step or, at most twice per step, is
         // the true-residual check that follows a small recursive residual or
         // the decision after it, so 3 * maxit + 6 iterations finish every system
@@ -1162,9 +1180,10 @@ spx_status cg_batch_run(spx_batch_system *sys, int32_t count, const BatchLayout 
             SPX_HIP(hipMemcpyAsync(wstate.data(), wstate_dev, sizeof(WideState) * wstate.size(), hipMemcpyDeviceToHost,
                                    stream));
             SPX_HIP(hipStreamSynchronize(stream));
-            bool all = true;
-            for (auto &w : wstate) all &= (w.mode == kWideDone);
-            if (all) break;
+            int32_t running = 0;
+            for (auto &w : wstate) running += (w.mode != kWideDone);
+            if (running == 0) break;
+            if (running < m.nlisted) SPX_CHECK(list());
         }
     }
     SPX_HIP(hipStreamSynchronize(stream));

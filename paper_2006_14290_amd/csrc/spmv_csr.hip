@@ -42,8 +42,9 @@ __global__ __launch_bounds__(kThreads) void csr_spmv_kernel(
     if (st != nullptr && st->flag != kRunning) return;
     const int64_t k = xcd_remap(blockIdx.x, grid_padded);
     if (k >= ntiles) return;
-    csr_tile<V, X, kEpi, kThreads, kTile, kVec, kLate>(k, nrows, nnz, ntiles, rowptr, col, val, x, y, alpha, beta,
-                                                       dot_with, dot_partials, part);
+    __shared__ __align__(16) unsigned char s_raw[csr_tile_lds<V, X, kTile, kLate>()];
+    csr_tile<V, X, kEpi, kThreads, kTile, kVec, kLate>(s_raw, k, nrows, nnz, ntiles, rowptr, col, val, x, y, alpha,
+                                                       beta, dot_with, dot_partials, part);
 }
 
 // Row-per-subwarp CSR product for short, regular rows (the "classical"

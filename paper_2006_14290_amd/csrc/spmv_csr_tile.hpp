@@ -49,8 +49,16 @@ __device__ inline int64_t lower_bound_wave(const int32_t *__restrict__ rowptr, i
 // kEpi: 0 = plain product; 1 = also sum_i y_i*w_i; 2 = also sum_i y_i*w_i
 // and sum_i y_i*y_i. With a solver state the sums are reduced across tiles
 // (deterministically, one partial per tile at dot_partials[j * ntiles + k]).
+// s_raw: csr_tile_lds<V, X, kTile, kLate>() bytes of LDS, 16-byte aligned.
+template <typename V, typename X, int kTile, bool kLate>
+constexpr size_t csr_tile_lds()
+{
+    return (size_t)(kTile + kCsrSlack) *
+           (kLate ? sizeof(int32_t) + sizeof(typename acc_of<V>::type) : sizeof(X));
+}
+
 template <typename V, typename X, int kEpi, int kThreads, int kTile, int kVec, bool kLate>
-__device__ __forceinline__ void csr_tile(int64_t k, int32_t nrows, int64_t nnz, int64_t ntiles,
+__device__ __forceinline__ void csr_tile(unsigned char *s_raw, int64_t k, int32_t nrows, int64_t nnz, int64_t ntiles,
                                          const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
                                          const V *__restrict__ val, const X *__restrict__ x, X *__restrict__ y,
                                          X alpha, X beta, const X *__restrict__ dot_with,
@@ -76,8 +84,6 @@ __device__ __forceinline__ void csr_tile(int64_t k, int32_t nrows, int64_t nnz, 
     // float once, while staging, instead of at every use in the row loop)
     using SV = typename acc_of<V>::type;
     typedef SV SVV __attribute__((ext_vector_type(kVec)));
-    constexpr size_t kLdsBytes = kLate ? (size_t)kStage * (sizeof(int32_t) + sizeof(SV)) : (size_t)kStage * sizeof(A);
-    __shared__ __align__(16) unsigned char s_raw[kLdsBytes];
     A *prod = reinterpret_cast<A *>(s_raw);
     SV *s_val = reinterpret_cast<SV *>(s_raw);
     int32_t *s_col = reinterpret_cast<int32_t *>(s_raw + (size_t)kStage * sizeof(SV));
