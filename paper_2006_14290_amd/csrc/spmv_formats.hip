@@ -1,8 +1,8 @@
 // spmv_formats.hip -- COO, ELL and hybrid ELL+COO products for gfx950.
 //
 // COO (Section 4: the Coo product "relies on atomic operations"): entries
-// sorted by row are cut into wavefront spans of a few chunks of kCooChunk
-// entries. A wavefront walks its span chunk by chunk (all loads of a chunk
+// sorted by row are cut into wavefront spans of a few chunks of 4 or 8 tiles
+// of 64 entries. A wavefront walks its span chunk by chunk (all loads of a chunk
 // issued first) in 64-entry tiles: coalesced loads of row, column and value,
 // gathered x, then one segmented inclusive scan across the 64 lanes (DPP row
 // shifts + row broadcasts, wave.hpp) keyed by the row index. The last segment
@@ -27,6 +27,9 @@
 #include "wave.hpp"
 
 namespace spx {
+
+constexpr int kEllSlots = 4;   // slot columns a thread has in flight (ELL: of two rows, mostly)
+constexpr int kSellSlots = 8;  // the same, SELL-P
 
 template <typename X>
 __device__ __forceinline__ X scaled(X v, X beta)
@@ -79,14 +82,24 @@ __device__ __forceinline__ void coo_write(int32_t r, X sum, bool chunk_start_seg
     }
 }
 
-template <typename V, typename X, bool kAccumulate, bool kBetaZero>
-__global__ __launch_bounds__(kCooThreads) void coo_spmv_kernel(int32_t nrows, int64_t nnz, int64_t nspans,
+// What bounds it: on scattered columns the gathers that miss the L2 caches (x
+// of 8 MB against 4 MB per XCD: 91 million 64-byte fills of 143 million
+// gathers, 3.7 TB/s, 1.54 ms); on stencils the scan of short segments
+// (7-point 160^3 float64 134 us, before 143).
+// 8 tiles: three wavefronts per SIMD (the loads in flight are enough, and
+// fewer rows' gathers share the L2 caches): float32 above 1008 -> 980 us,
+// 300,000 Zipf rows float64 331 -> 327; on stencils with 4 tiles it loses 20 %.
+template <typename V, typename X, bool kAccumulate, bool kBetaZero, int kCooTiles>
+__global__ __launch_bounds__(kCooThreads)
+__attribute__((amdgpu_waves_per_eu(kCooTiles == kCooTilesLarge ? 3 : 1, kCooTiles == kCooTilesLarge ? 3 : 8)))
+void coo_spmv_kernel(int32_t nrows, int64_t nnz, int64_t nspans,
                                                                int64_t span, int64_t grid_padded,
                                                                const int32_t *__restrict__ row,
                                                                const int32_t *__restrict__ col,
                                                                const V *__restrict__ val, const X *__restrict__ x,
                                                                X *__restrict__ y, X alpha, X beta)
 {
+    constexpr int kCooChunk = kCooTiles * kWave;  // entries per wavefront chunk
     const int lane = lane_id();
     const int64_t blk = xcd_remap(blockIdx.x, grid_padded);
     const int64_t w = blk * (kCooThreads / kWave) + threadIdx.x / kWave;
@@ -125,9 +138,13 @@ __global__ __launch_bounds__(kCooThreads) void coo_spmv_kernel(int32_t nrows, in
             }
         }
         const int32_t chunk_before = c0 > 0 ? row[c0 - 1] : -1;
+        // all gathers together: a load under a per-lane branch together with
+        // its use would be waited for before the next one is issued
+        X xv[kCooTiles];
 #pragma unroll
-        for (int t = 0; t < kCooTiles; ++t)
-            if (r[t] >= 0) p[t] *= x[c[t]];
+        for (int t = 0; t < kCooTiles; ++t) xv[t] = x[c[t]];  // column 0 past the end
+#pragma unroll
+        for (int t = 0; t < kCooTiles; ++t) p[t] = r[t] >= 0 ? p[t] * xv[t] : X(0);
 
 #pragma unroll
         for (int t = 0; t < kCooTiles; ++t) {
@@ -181,8 +198,15 @@ __global__ __launch_bounds__(kCooThreads) void coo_spmv_kernel(int32_t nrows, in
 }
 
 // One thread per kR consecutive rows (kR = 2 loads the two rows' slots as
-// one vector when ld is even and the arrays are aligned), four slot columns
-// in flight; a wavefront stops once all its rows are into their padding.
+// one vector when ld is even and the arrays are aligned), kEllSlots slot
+// columns gathered together while the next ones are loaded; a wavefront stops
+// once all its rows are into their padding.
+// What bounds it: the slot stream; a gather under the same branch as its use
+// is waited for alone, so the gathers of a block come before its sums. Before
+// -> after, one MI355X, cold matrices: 7-point 160^3 binary16 45.4 -> 40.1 us,
+// float64 161^3 83.0 -> 79.6 (4.9 TB/s), 27-point 101^3 float32 43.6 -> 41.2,
+// 64^2 grid 4.9 -> 3.8 us. Six and eight slot columns: 27-point float64 69.0
+// and 70.5 us against 67.1.
 // kEpi: 0 = plain product; 1 = also the block's sum of y_i*w_i; 2 = that and
 // the sum of y_i^2 (one partial per work-group, reduced later in a fixed
 // order; a set solver flag skips the launch).
@@ -205,35 +229,47 @@ __global__ __launch_bounds__(kEllThreads) void ell_spmv_kernel(int32_t nrows, in
     X sum[kR];
 #pragma unroll
     for (int r = 0; r < kR; ++r) sum[r] = X(0);
-    constexpr int U = 4;
-    for (int k = 0; k < K; k += U) {
-        CR cc[U];
-        VR vv[U];
+    if (K > 0) {
+        constexpr int U = kEllSlots;
+        // slots [k, k + U) of the thread's rows
+        auto load = [&](int k, CR(&c)[U], VR(&v)[U]) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-#pragma unroll
-            for (int r = 0; r < kR; ++r) {
-                cc[u][r] = -1;
-                vv[u][r] = V(0);
+            for (int u = 0; u < U; ++u) {
+                if (k + u >= K) break;
+                const int64_t q = (int64_t)(k + u) * ld + (in ? i0 : 0);
+                c[u] = ld_stream(reinterpret_cast<const CR *>(ecol + q));
+                v[u] = ld_stream(reinterpret_cast<const VR *>(eval + q));
             }
-            if (in && k + u < K) {
-                const int64_t q = (int64_t)(k + u) * ld + i0;
-                cc[u] = ld_stream(reinterpret_cast<const CR *>(ecol + q));
-                vv[u] = ld_stream(reinterpret_cast<const VR *>(eval + q));
+        };
+        CR cc[U], cn[U];
+        VR vv[U], vn[U];
+        load(0, cc, vv);
+        for (int k = 0;; k += U) {
+            const bool more = k + U < K;
+            if (more) load(k + U, cn, vn);  // on their way while this block's gathers are
+            X xv[U][kR];
+            bool live = false;
 #pragma unroll
-                for (int r = 1; r < kR; ++r)
-                    if (i0 + r >= nrows) cc[u][r] = -1;  // a slot past the last row is not the matrix's
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < kR; ++r) {
+                    if (!(in && k + u < K && i0 + r < nrows)) cc[u][r] = -1;
+                    xv[u][r] = X(0);
+                    if (cc[u][r] >= 0) xv[u][r] = x[cc[u][r]];
+                    if (u == U - 1) live |= cc[u][r] >= 0;
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < kR; ++r)
+                    if (cc[u][r] >= 0) sum[r] += widen(vv[u][r]) * xv[u][r];
+            if (!more || ballot64(live) == 0) break;  // or every row of the wavefront is into its padding
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                cc[u] = cn[u];
+                vv[u] = vn[u];
             }
         }
-        bool live = false;
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int r = 0; r < kR; ++r)
-                if (cc[u][r] >= 0) sum[r] += widen(vv[u][r]) * x[cc[u][r]];
-#pragma unroll
-        for (int r = 0; r < kR; ++r) live |= cc[U - 1][r] >= 0;
-        if (ballot64(live) == 0) break;  // every row of the wavefront is into its padding
     }
     X d1 = X(0), d2 = X(0);
 #pragma unroll
@@ -268,11 +304,14 @@ static spx_status coo_part(int32_t nrows, int64_t nnz, const int32_t *row, const
         return SPX_OK;
     }
     // chunks per wavefront span: enough spans to fill the GPU several times
-    // over, at most kCooMaxSpan chunks (fewer spans, fewer boundary atomics)
-    const int64_t nchunks = ceil_div(nnz, kCooChunk);
+    // over, at most `most` chunks (fewer spans, fewer boundary atomics)
+    const bool large = nnz >= kCooLargeNnz;
+    const int64_t chunk = (int64_t)kWave * (large ? kCooTilesLarge : kCooTilesSmall);
+    const int64_t most = large ? kCooSpanLarge : kCooSpanSmall;
+    const int64_t nchunks = ceil_div(nnz, chunk);
     int64_t per = ceil_div(nchunks, kCooTargetSpans);
-    per = per < 1 ? 1 : (per > kCooMaxSpan ? kCooMaxSpan : per);
-    const int64_t span = per * kCooChunk;
+    per = per < 1 ? 1 : (per > most ? most : per);
+    const int64_t span = per * chunk;
     const int64_t nspans = ceil_div(nnz, span);
     if (!kAccumulate && nspans > 1) {
         coo_split_init_kernel<X><<<(unsigned)ceil_div(nspans - 1, 256), 256, 0, stream>>>(nnz, nspans, span, row, y,
@@ -281,12 +320,17 @@ static spx_status coo_part(int32_t nrows, int64_t nnz, const int32_t *row, const
     }
     const int64_t blocks = ceil_div(nspans, kCooThreads / kWave);
     const int64_t grid = pad_to_xcds(blocks);
-    if (!kAccumulate && beta == X(0))
-        coo_spmv_kernel<V, X, false, true><<<(unsigned)grid, kCooThreads, 0, stream>>>(
-            nrows, nnz, nspans, span, grid, row, col, val, x, y, alpha, beta);
-    else
-        coo_spmv_kernel<V, X, kAccumulate, false><<<(unsigned)grid, kCooThreads, 0, stream>>>(
-            nrows, nnz, nspans, span, grid, row, col, val, x, y, alpha, beta);
+#define SPX_COO_LAUNCH(BZ, TILES)                                                                                   \
+    coo_spmv_kernel<V, X, kAccumulate, BZ, TILES><<<(unsigned)grid, kCooThreads, 0, stream>>>(                      \
+        nrows, nnz, nspans, span, grid, row, col, val, x, y, alpha, beta)
+    if (!kAccumulate && beta == X(0)) {
+        if (large) SPX_COO_LAUNCH(!kAccumulate, kCooTilesLarge);
+        else SPX_COO_LAUNCH(!kAccumulate, kCooTilesSmall);
+    } else {
+        if (large) SPX_COO_LAUNCH(false, kCooTilesLarge);
+        else SPX_COO_LAUNCH(false, kCooTilesSmall);
+    }
+#undef SPX_COO_LAUNCH
     SPX_LAUNCHED();
     return SPX_OK;
 }
@@ -349,6 +393,56 @@ spx_status hyb_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X bet
                                 beta, stream);
 }
 
+// What bounds the SELL-P products: the slot stream (see the ELL kernel).
+// Before -> after, 64-row slices: 27-point 101^3 float32 48.9 -> 39.1 us
+// (5.9 TB/s), float64 67.6 -> 64.6, 7-point 160^3 binary16 60.5 -> 39.3 us.
+// 4, 6 and 12 slot columns at a time, the same cases: 37.7 / 37.5 / 41.9,
+// 62.3 / 62.6 / 65.8 and 46.4 / 50.3 / 46.8 us against 38.1, 64.0 and 39.6.
+// One row's sum over slot columns k, k + step, ... below w (slot column k of
+// the row at k * C): kSellSlots columns at a time, the next ones loaded while
+// this block's gathers are in flight. Columns past the last are read again
+// and dropped; the entries are added in order.
+template <typename V, typename X>
+__device__ __forceinline__ X slot_sum(const int32_t *__restrict__ cs, const V *__restrict__ vs, int32_t k,
+                                      int32_t step, int32_t w, int32_t C, const X *__restrict__ x)
+{
+    constexpr int U = kSellSlots;
+    X sum = X(0);
+    if (k >= w) return sum;
+    auto load = [&](int32_t j, int32_t(&c)[U], V(&v)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t q = (int64_t)(j + u * step < w ? j + u * step : j) * C;
+            c[u] = ld_stream(cs + q);
+            v[u] = ld_stream(vs + q);
+        }
+    };
+    int32_t cc[U], cn[U];
+    V vv[U], vn[U];
+    load(k, cc, vv);
+    while (true) {
+        const int32_t next = k + U * step;
+        if (next < w) load(next, cn, vn);
+        X xv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (k + u * step >= w) cc[u] = -1;
+            xv[u] = X(0);
+            if (cc[u] >= 0) xv[u] = x[cc[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (cc[u] >= 0) sum += widen(vv[u]) * xv[u];
+        if (next >= w) return sum;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            cc[u] = cn[u];
+            vv[u] = vn[u];
+        }
+        k = next;
+    }
+}
+
 // SELL-P: one work-group of kSellThreads per slice. Lane l = tid % C owns row
 // s*C + l; the G = kSellThreads / C lane groups take the slice's slot
 // columns round robin (group g: columns g, g + G, ...), each slot column
@@ -377,28 +471,7 @@ __global__ __launch_bounds__(kSellThreads) void sellp_spmv_kernel(int32_t nrows,
     const int32_t k0 = sets[s], w = sets[s + 1] - k0;
     const int32_t *__restrict__ cs = scol + (int64_t)k0 * C + l;
     const V *__restrict__ vs = sval + (int64_t)k0 * C + l;
-    X sum = X(0);
-    constexpr int U = 4;
-    int32_t k = g;
-    for (; k + (U - 1) * G < w; k += U * G) {
-        int32_t cc[U];
-        X vv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t q = (int64_t)(k + u * G) * C;
-            cc[u] = ld_stream(cs + q);
-            vv[u] = widen(ld_stream(vs + q));
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (cc[u] >= 0) sum += vv[u] * x[cc[u]];
-    }
-    for (; k < w; k += G) {
-        const int64_t q = (int64_t)k * C;
-        const int32_t c = ld_stream(cs + q);
-        const X v = widen(ld_stream(vs + q));
-        if (c >= 0) sum += v * x[c];
-    }
+    const X sum = slot_sum(cs, vs, g, G, w, C, x);
     part[tid] = sum;
     __syncthreads();
     const int64_t row = s * C + l;
@@ -446,26 +519,7 @@ __global__ __launch_bounds__(kSellThreads) void sellp64_spmv_kernel(int32_t nrow
         const int32_t k0 = sets[s], w = sets[s + 1] - k0;
         const int32_t *__restrict__ cs = scol + (int64_t)k0 * kWave + l;
         const V *__restrict__ vs = sval + (int64_t)k0 * kWave + l;
-        X sum = X(0);
-        constexpr int U = 4;
-        int32_t k = 0;
-        for (; k + U <= w; k += U) {
-            int32_t cc[U];
-            X vv[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                cc[u] = ld_stream(cs + (int64_t)(k + u) * kWave);
-                vv[u] = widen(ld_stream(vs + (int64_t)(k + u) * kWave));
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (cc[u] >= 0) sum += vv[u] * x[cc[u]];
-        }
-        for (; k < w; ++k) {
-            const int32_t c = ld_stream(cs + (int64_t)k * kWave);
-            const X v = widen(ld_stream(vs + (int64_t)k * kWave));
-            if (c >= 0) sum += v * x[c];
-        }
+        const X sum = slot_sum(cs, vs, 0, 1, w, kWave, x);
         const int64_t row = s * kWave + l;
         if (row < nrows) {
             X out = alpha * sum;
