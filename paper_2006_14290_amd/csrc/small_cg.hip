@@ -1,7 +1,7 @@
 // small_cg.hip -- CG for small systems on one work-group (the latency path).
 //
 // A system of a few thousand rows moves well under a megabyte per CG
-// iteration, so the five launches per iteration of the general driver are
+// iteration, so the three launches per iteration of the general driver are
 // pure launch latency. Here one work-group of 1024 threads runs the whole
 // solve in a single launch: thread t owns rows t, t + 1024, ... (up to kR = 4
 // of them: four rows' state fits the 128 registers a thread of a 1024-thread
@@ -55,8 +55,14 @@ __device__ __forceinline__ double small_row(int32_t a, int32_t b, const int32_t 
 
 // kThreads threads, kR rows per thread; kL > 0: every row has at most kL
 // entries and each thread keeps its rows' columns and values in registers
-// for the whole solve (the product then only gathers p from LDS); kL = 0:
-// the entries are read from global memory at every product.
+// for the whole solve (the product then only gathers p from LDS; slots past a
+// row's end hold value 0 and point at a zero behind the vector, so that no
+// branch separates the gathers); kL = 0: the entries are read from global
+// memory at every product.
+// What bounds it: the chain of an iteration (gathers, two work-group sums,
+// three barriers). 64^2 Poisson grid, one MI355X: 3.35 us per iteration with
+// a branch around each gather (each then waited for alone), 2.7 without; 512
+// threads with 8 rows each 2.85; p in registers as well spills (3.9).
 template <int kThreads, int kR, int kL>
 __global__ __launch_bounds__(kThreads) void small_cg_kernel(int32_t n, const int32_t *__restrict__ rowptr,
                                                                 const int32_t *__restrict__ col,
@@ -66,10 +72,11 @@ __global__ __launch_bounds__(kThreads) void small_cg_kernel(int32_t n, const int
                                                                 KState *st)
 {
     constexpr int kWaves = kThreads / kWave;
-    __shared__ double s_v[kThreads * kR];  // p (or x while the true residual is formed)
+    __shared__ double s_v[kThreads * kR + 1];  // p (or x while the true residual is formed), and a zero
     __shared__ double s_red[2][4 * kMaxWaves];
     int par = 0;
     const int tid = threadIdx.x;
+    if (tid == 0) s_v[kThreads * kR] = 0.0;
     const double tol2 = st->tol2;
     const int32_t maxit = st->maxit;
     int32_t ra[kR], rb[kR];
@@ -84,9 +91,11 @@ __global__ __launch_bounds__(kThreads) void small_cg_kernel(int32_t n, const int
         dv[k] = in ? (dinv ? dinv[i] : 1.0) : 0.0;
         if (!x0_zero) s_v[i] = xr[k];
     }
-    int32_t cc[kL > 0 ? kR : 1][kL > 0 ? kL : 1];
+    // columns as 16-bit byte offsets into s_v, two to a register
+    static_assert(kL == 0 || kThreads * kR * sizeof(double) <= 0xffff, "byte offsets of 16 bits");
+    constexpr int kPairs = (kL + 1) / 2;
+    uint32_t cc[kL > 0 ? kR : 1][kL > 0 ? kPairs : 1];
     double vv[kL > 0 ? kR : 1][kL > 0 ? kL : 1];
-    int32_t ln[kL > 0 ? kR : 1];  // row lengths (the cached form needs nothing else)
     if constexpr (kL > 0) {
         // the row-length hint is only a hint: a longer row sends the solve back
         // to the host, which runs the streaming form instead
@@ -99,22 +108,30 @@ __global__ __launch_bounds__(kThreads) void small_cg_kernel(int32_t n, const int
         }
 #pragma unroll
         for (int k = 0; k < kR; ++k) {
-            ln[k] = rb[k] - ra[k];
+#pragma unroll
+            for (int e = 0; e < kPairs; ++e) cc[k][e] = 0;
 #pragma unroll
             for (int e = 0; e < kL; ++e) {
-                const bool in = e < ln[k];
-                cc[k][e] = in ? col[ra[k] + e] : 0;
+                const bool in = e < rb[k] - ra[k];
+                const uint32_t at = (in ? (uint32_t)col[ra[k] + e] : kThreads * kR) * (uint32_t)sizeof(double);
+                cc[k][e / 2] |= at << (16 * (e % 2));
                 vv[k][e] = in ? val[ra[k] + e] : 0.0;
             }
         }
     }
+    const int32_t wave0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));  // the wavefront's first row
     // product of row k with v (in LDS), entries in order
     auto row = [&](int k, const double *v) -> double {
         if constexpr (kL > 0) {
+            if (wave0 + k * kThreads >= n) return 0.0;  // rows the system does not have
             double t = 0.0;
 #pragma unroll
-            for (int e = 0; e < kL; ++e)
-                if (e < ln[k]) t += vv[k][e] * v[cc[k][e]];
+            for (int e = 0; e < kPairs; ++e) asm volatile("" : "+v"(cc[k][e]));  // unpacked here, not kept unpacked
+#pragma unroll
+            for (int e = 0; e < kL; ++e) {
+                const uint32_t at = e % 2 ? cc[k][e / 2] >> 16 : cc[k][e / 2] & 0xffffu;
+                t += vv[k][e] * *reinterpret_cast<const double *>(reinterpret_cast<const char *>(v) + at);
+            }
             return t;
         } else {
             return small_row(ra[k], rb[k], col, val, v);
@@ -259,8 +276,8 @@ spx_status small_cg_launch(const spx_matrix &A, const double *b, double *x, cons
                            bool cached, KState *st, hipStream_t stream)
 {
     const double *val = static_cast<const double *>(A.vals);
-    if (cached)  // rows of at most 5 entries: 512 threads, 8 rows each, matrix in registers
-        small_cg_kernel<512, 8, 5><<<1, 512, 0, stream>>>(A.nrows, A.rowptr, A.colidx, val, b, x, dinv, x0_zero, st);
+    if (cached)  // rows of at most 5 entries: matrix in registers
+        small_cg_kernel<1024, 4, 5><<<1, 1024, 0, stream>>>(A.nrows, A.rowptr, A.colidx, val, b, x, dinv, x0_zero, st);
     else
         small_cg_kernel<kSmallThreads, kSmallMaxRows / kSmallThreads, 0><<<1, kSmallThreads, 0, stream>>>(
             A.nrows, A.rowptr, A.colidx, val, b, x, dinv, x0_zero, st);
