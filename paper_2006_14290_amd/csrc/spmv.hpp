@@ -16,13 +16,16 @@ spx_status spmv_dispatch(const spx_matrix &A, const void *x, void *y, double alp
 
 constexpr int kCooThreads = 256;
 // 64-entry tiles per wavefront chunk. Large matrices (kCooLargeNnz entries)
-// take the larger chunks and longer spans: fewer open rows and atomics, still
-// tens of thousands of spans. Zipf rows, 143 million entries, float64 hybrid:
-// 1556 us with 4 tiles and spans of 8 chunks, 1541 with 8 and 16, float32
-// 1020 / 981; 800,000 entries: 7.3 / 9.6 us.
+// whose x fits one XCD's L2 (kCooCachedX bytes) take larger chunks and longer
+// spans: fewer open rows and atomics, still tens of thousands of spans. Zipf
+// rows, float32, 153 million entries: 1028 us with 4 tiles and spans of 8
+// chunks, 963 with 8 and 16; 800,000 entries 7.3 / 9.6. With a larger x the
+// gathers' line fills bind: more of them in flight take as long or longer
+// (float64, 1595 us tile by tile, 1617 with 8 tiles together, cold).
 constexpr int kCooTilesSmall = 4, kCooTilesLarge = 8;
 constexpr int64_t kCooSpanSmall = 8, kCooSpanLarge = 16;  // chunks per span at most
 constexpr int64_t kCooLargeNnz = int64_t(1) << 25;
+constexpr int64_t kCooCachedX = int64_t(4) << 20;
 constexpr int64_t kCooTargetSpans = 16384;  // wavefront spans to aim for
 constexpr int kEllThreads = 256;
 constexpr int kSellThreads = 256;

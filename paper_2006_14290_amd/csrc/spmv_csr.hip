@@ -199,7 +199,10 @@ static void stage_launch(const spx_matrix &A, int len, const X *x, X *y, X alpha
     const int32_t nblk = (int32_t)ceil_div(A.nrows, stage_rows(A, len));
     const int32_t nnz8 = (int32_t)(A.nnz & ~(int64_t)7);
     const unsigned grid = (unsigned)stage_grid(A, len);
-#define SPX_STAGE(SIZE, ROWS, LEN, CAP)                                                                                csr_stage_kernel<V, X, kEpi, SIZE, ROWS, LEN, CAP><<<grid, kStageWaves * kWave, 0, stream>>>(                          A.nrows, nnz8, nblk, A.rowptr, A.colidx, static_cast<const V *>(A.vals), x, y, alpha, beta, dot_with,              dot_partials, st)
+#define SPX_STAGE(SIZE, ROWS, LEN, CAP)                                                                             \
+    csr_stage_kernel<V, X, kEpi, SIZE, ROWS, LEN, CAP><<<grid, kStageWaves * kWave, 0, stream>>>(                   \
+        A.nrows, nnz8, nblk, A.rowptr, A.colidx, static_cast<const V *>(A.vals), x, y, alpha, beta, dot_with,       \
+        dot_partials, st)
     if constexpr (sizeof(V) == 8) {
         switch (len) {
         case 8: SPX_STAGE(1, 1, 8, 512); break;

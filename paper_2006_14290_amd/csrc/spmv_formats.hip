@@ -83,13 +83,14 @@ __device__ __forceinline__ void coo_write(int32_t r, X sum, bool chunk_start_seg
 }
 
 // What bounds it: on scattered columns the gathers that miss the L2 caches (x
-// of 8 MB against 4 MB per XCD: 91 million 64-byte fills of 143 million
-// gathers, 3.7 TB/s, 1.54 ms); on stencils the scan of short segments
+// of 8 MB against 4 MB per XCD: 153 million gathers and the stream make 91
+// million 128-byte fills, 11.6 GB in 1.54 ms, 7.5 TB/s); on stencils the scan of short segments
 // (7-point 160^3 float64 134 us, before 143).
 // 8 tiles: three wavefronts per SIMD (the loads in flight are enough, and
 // fewer rows' gathers share the L2 caches): float32 above 1008 -> 980 us,
 // 300,000 Zipf rows float64 331 -> 327; on stencils with 4 tiles it loses 20 %.
-template <typename V, typename X, bool kAccumulate, bool kBetaZero, int kCooTiles>
+// kTogether: a chunk's gathers go out together; otherwise tile by tile.
+template <typename V, typename X, bool kAccumulate, bool kBetaZero, int kCooTiles, bool kTogether>
 __global__ __launch_bounds__(kCooThreads)
 __attribute__((amdgpu_waves_per_eu(kCooTiles == kCooTilesLarge ? 3 : 1, kCooTiles == kCooTilesLarge ? 3 : 8)))
 void coo_spmv_kernel(int32_t nrows, int64_t nnz, int64_t nspans,
@@ -138,13 +139,19 @@ void coo_spmv_kernel(int32_t nrows, int64_t nnz, int64_t nspans,
             }
         }
         const int32_t chunk_before = c0 > 0 ? row[c0 - 1] : -1;
-        // all gathers together: a load under a per-lane branch together with
-        // its use would be waited for before the next one is issued
-        X xv[kCooTiles];
+        if constexpr (kTogether) {
+            // a load under a per-lane branch together with its use would be
+            // waited for before the next one is issued
+            X xv[kCooTiles];
 #pragma unroll
-        for (int t = 0; t < kCooTiles; ++t) xv[t] = x[c[t]];  // column 0 past the end
+            for (int t = 0; t < kCooTiles; ++t) xv[t] = x[c[t]];  // column 0 past the end
 #pragma unroll
-        for (int t = 0; t < kCooTiles; ++t) p[t] = r[t] >= 0 ? p[t] * xv[t] : X(0);
+            for (int t = 0; t < kCooTiles; ++t) p[t] = r[t] >= 0 ? p[t] * xv[t] : X(0);
+        } else {
+#pragma unroll
+            for (int t = 0; t < kCooTiles; ++t)
+                if (r[t] >= 0) p[t] *= x[c[t]];
+        }
 
 #pragma unroll
         for (int t = 0; t < kCooTiles; ++t) {
@@ -204,8 +211,8 @@ void coo_spmv_kernel(int32_t nrows, int64_t nnz, int64_t nspans,
 // What bounds it: the slot stream; a gather under the same branch as its use
 // is waited for alone, so the gathers of a block come before its sums. Before
 // -> after, one MI355X, cold matrices: 7-point 160^3 binary16 45.4 -> 40.1 us,
-// float64 161^3 83.0 -> 79.6 (4.9 TB/s), 27-point 101^3 float32 43.6 -> 41.2,
-// 64^2 grid 4.9 -> 3.8 us. Six and eight slot columns: 27-point float64 69.0
+// float64 161^3 83.0 -> 79.6 (4.9 TB/s), 27-point 100^3 float32 44.8 -> 38.1
+// (5.9 TB/s), 64^2 grid 4.9 -> 3.8 us. Six and eight slot columns: 27-point float64 69.0
 // and 70.5 us against 67.1.
 // kEpi: 0 = plain product; 1 = also the block's sum of y_i*w_i; 2 = that and
 // the sum of y_i^2 (one partial per work-group, reduced later in a fixed
@@ -293,7 +300,7 @@ __global__ __launch_bounds__(kEllThreads) void ell_spmv_kernel(int32_t nrows, in
 }
 
 template <typename V, typename X, bool kAccumulate>
-static spx_status coo_part(int32_t nrows, int64_t nnz, const int32_t *row, const int32_t *col, const V *val,
+static spx_status coo_part(int32_t nrows, int32_t ncols, int64_t nnz, const int32_t *row, const int32_t *col, const V *val,
                            const X *x, X *y, X alpha, X beta, hipStream_t stream)
 {
     if (nnz == 0) {
@@ -305,7 +312,8 @@ static spx_status coo_part(int32_t nrows, int64_t nnz, const int32_t *row, const
     }
     // chunks per wavefront span: enough spans to fill the GPU several times
     // over, at most `most` chunks (fewer spans, fewer boundary atomics)
-    const bool large = nnz >= kCooLargeNnz;
+    const bool large = nnz >= kCooLargeNnz && ncols * (int64_t)sizeof(X) <= kCooCachedX;
+    const bool missing = nnz >= kCooLargeNnz && !large;
     const int64_t chunk = (int64_t)kWave * (large ? kCooTilesLarge : kCooTilesSmall);
     const int64_t most = large ? kCooSpanLarge : kCooSpanSmall;
     const int64_t nchunks = ceil_div(nnz, chunk);
@@ -320,15 +328,17 @@ static spx_status coo_part(int32_t nrows, int64_t nnz, const int32_t *row, const
     }
     const int64_t blocks = ceil_div(nspans, kCooThreads / kWave);
     const int64_t grid = pad_to_xcds(blocks);
-#define SPX_COO_LAUNCH(BZ, TILES)                                                                                   \
-    coo_spmv_kernel<V, X, kAccumulate, BZ, TILES><<<(unsigned)grid, kCooThreads, 0, stream>>>(                      \
+#define SPX_COO_LAUNCH(BZ, TILES, TOGETHER)                                                                         \
+    coo_spmv_kernel<V, X, kAccumulate, BZ, TILES, TOGETHER><<<(unsigned)grid, kCooThreads, 0, stream>>>(            \
         nrows, nnz, nspans, span, grid, row, col, val, x, y, alpha, beta)
     if (!kAccumulate && beta == X(0)) {
-        if (large) SPX_COO_LAUNCH(!kAccumulate, kCooTilesLarge);
-        else SPX_COO_LAUNCH(!kAccumulate, kCooTilesSmall);
+        if (large) SPX_COO_LAUNCH(!kAccumulate, kCooTilesLarge, true);
+        else if (missing) SPX_COO_LAUNCH(!kAccumulate, kCooTilesSmall, false);
+        else SPX_COO_LAUNCH(!kAccumulate, kCooTilesSmall, true);
     } else {
-        if (large) SPX_COO_LAUNCH(false, kCooTilesLarge);
-        else SPX_COO_LAUNCH(false, kCooTilesSmall);
+        if (large) SPX_COO_LAUNCH(false, kCooTilesLarge, true);
+        else if (missing) SPX_COO_LAUNCH(false, kCooTilesSmall, false);
+        else SPX_COO_LAUNCH(false, kCooTilesSmall, true);
     }
 #undef SPX_COO_LAUNCH
     SPX_LAUNCHED();
@@ -338,21 +348,25 @@ static spx_status coo_part(int32_t nrows, int64_t nnz, const int32_t *row, const
 template <typename V, typename X>
 spx_status coo_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X beta, hipStream_t stream)
 {
-    return coo_part<V, X, false>(A.nrows, A.nnz, A.rowidx, A.colidx, static_cast<const V *>(A.vals), x, y, alpha,
+    return coo_part<V, X, false>(A.nrows, A.ncols, A.nnz, A.rowidx, A.colidx, static_cast<const V *>(A.vals), x, y, alpha,
                                  beta, stream);
 }
 
 // Two rows per thread when the slot columns can be read two rows at a time:
 // even leading dimension (so a pair never straddles a slot column; with an
 // odd nrows the last pair's second row is in-bounds padding) and arrays
-// aligned to two entries.
+// aligned to two entries. Not float32: a pair's gathers share lines and go out
+// together, and the float32 stream is better off with one row per lane.
+// Pairs against single rows, cold: 27-point 100^3 float64 61.5 / 62.6 us,
+// float32 50.2 / 38.1, binary16 36.4 / 41.6; 7-point 160^3 float64 70.8 / 70.7,
+// float32 50.2 / 44.6, binary16 40.2 / 49.2.
 static int ell_rows_per_thread(const spx_matrix &A)
 {
     const size_t sv = A.val_type == SPX_F64 ? 8 : (A.val_type == SPX_F32 ? 4 : 2);
     const bool even = (A.ell_ld % 2) == 0;
     const bool aligned = (reinterpret_cast<uintptr_t>(A.ell_col) % 8 == 0) &&
                          (reinterpret_cast<uintptr_t>(A.ell_val) % (2 * sv) == 0);
-    return even && aligned ? 2 : 1;
+    return even && aligned && A.val_type != SPX_F32 ? 2 : 1;
 }
 
 int64_t ell_dot_parts(const spx_matrix &A)
@@ -389,7 +403,7 @@ template <typename V, typename X>
 spx_status hyb_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X beta, hipStream_t stream)
 {
     SPX_CHECK(ell_spmv_launch<V, X>(A, x, y, alpha, beta, stream));
-    return coo_part<V, X, true>(A.nrows, A.coo_nnz, A.rowidx, A.colidx, static_cast<const V *>(A.vals), x, y, alpha,
+    return coo_part<V, X, true>(A.nrows, A.ncols, A.coo_nnz, A.rowidx, A.colidx, static_cast<const V *>(A.vals), x, y, alpha,
                                 beta, stream);
 }
 

@@ -73,11 +73,13 @@ def test_infinity_reaches_its_own_rows_only(fmt):
 @pytest.mark.parametrize("per", [31, 33])
 def test_coo_chunks_of_large_matrices(per):
     """Entry counts around the step to larger chunks (2^25 entries)."""
-    n = (1 << 20) - (per == 33) * 17
+    n = (1 << 20) - (per == 33) * 17  # 4 MB in float32
     print(f"case coo {n} rows of {per}", flush=True)
     off = np.sort(np.random.default_rng(per).choice(4 * per, per, replace=False))
     col = np.minimum(np.arange(n)[:, None], n - 4 * per) + off
     A = S.CSR(n, (np.arange(n + 1) * per).astype(np.int32), col.reshape(-1).astype(np.int32),
               np.random.default_rng(1).uniform(-1, 1, n * per))
-    check(A, spx.convert(spx.csr_from_host(A), spx.COO), "f64", 1.0, 0.0)
-    check(A, spx.convert(spx.csr_from_host(A), spx.HYB, ell_width=1), "f64", -1.5, 0.5)
+    for dtype in ("f64", "f32"):  # x of more and of at most 4 MB
+        Ad = spx.csr_from_host(A, spx.DTYPE_NAMES[dtype])
+        check(A, spx.convert(Ad, spx.COO), dtype, 1.0, 0.0)
+        check(A, spx.convert(Ad, spx.HYB, ell_width=1), dtype, -1.5, 0.5)
