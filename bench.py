@@ -229,14 +229,22 @@ def subwarp_sweep(spx, torch, dev):
 
 def csr_kernel_name(M):
     """Name of the CSR kernel the library picks for M (mirrors its rule:
-    row-per-subwarp when rows are short and even, else load-balanced)."""
-    if M is None or M.max_row_len <= 0 or M.nnz <= 0 or M.nrows > 65536:
+    staged rows when they are short and even, else row-per-subwarp on small
+    matrices, else load-balanced)."""
+    if M is None or M.max_row_len <= 0 or M.nnz <= 0:
         return "csr_spmv_kernel (load-balanced)"
+    length = 8
+    while length < M.max_row_len:
+        length *= 2
+    if M.nnz >= 8192 and length <= 128 and 2 * M.nnz >= length * M.nrows:
+        return f"csr_stage_kernel (rows of up to {length})"
     mean = -(-M.nnz // M.nrows)
     sub = 4
     while sub < 64 and sub < mean:
         sub *= 2
-    return f"csr_rows_kernel (subwarp {sub})" if M.max_row_len <= 2 * sub else "csr_spmv_kernel (load-balanced)"
+    if M.nrows <= 32768 and M.max_row_len <= 2 * sub:
+        return f"csr_rows_kernel (subwarp {sub})"
+    return "csr_spmv_kernel (load-balanced)"
 
 
 def profile_traffic(name, algo_bytes):

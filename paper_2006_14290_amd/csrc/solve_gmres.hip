@@ -27,7 +27,8 @@
 // H y = g there; then x += M^{-1} V y, and the next cycle starts from the true
 // residual b - A x.
 //
-// What bounds a step: the basis, (j + 1) n values per pass, read at 6.2 TB/s.
+// What bounds a step: the basis, (j + 1) n values per pass, read at 5.6 to 6
+// TB/s.
 // GMRES(30) + Jacobi, convection-diffusion 128^3, one MI355X: 283 us per step
 // with four passes, 100 barriers per work-group and a normalising kernel,
 // 202 us now.

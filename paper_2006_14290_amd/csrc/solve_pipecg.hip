@@ -15,7 +15,7 @@
 //   3. z = nv + beta z, q = m + beta q, s = w + beta s, p = u + beta p,
 //      x += alpha p, r -= alpha s, u -= alpha q, w -= alpha z, m = M^{-1} w,
 //      with the partial sums of r.u, w.u and r.r.
-// Against CG's five launches it moves more vector bytes (the update touches
+// Against CG's three launches it moves more vector bytes (the update touches
 // 20 vectors with Jacobi, 13 without, against CG's 11): on one GPU it pays
 // where launches and reductions dominate (small systems); across GPUs the one
 // reduction per iteration is the point. Scalars stay on the device and
