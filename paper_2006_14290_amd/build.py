@@ -6,7 +6,8 @@ parallel), then linked into paper_2006_14290_amd/libspx.so. Always rebuilds.
 build_hostsan() builds a second copy, libspx_hostsan.so, whose host code is
 instrumented with AddressSanitizer and UBSan (device code is compiled as
 usual), and the test driver tests/sanitize/abi_driver_hostsan linked against
-it, which the sanitizer tests run.
+it, which the sanitizer tests run. build_tests() builds the tests' own kernels
+(tests/native), which call device functions that no entry point exposes.
 """
 from __future__ import annotations
 
@@ -24,6 +25,8 @@ LIB_HOSTSAN = os.path.join(HERE, "libspx_hostsan.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 DRIVER_SRC = os.path.join(os.path.dirname(HERE), "tests", "sanitize", "abi_driver.cpp")
 DRIVER_HOSTSAN = os.path.join(os.path.dirname(HERE), "tests", "sanitize", "abi_driver_hostsan")
+TESTS_SRC = os.path.join(os.path.dirname(HERE), "tests", "native", "wave_sums.hip")
+TESTS_LIB = os.path.join(os.path.dirname(HERE), "tests", "native", "libwave_sums.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.environ.get("HIPCC", os.path.join(ROCM, "bin", "hipcc"))
 CLANGXX = os.path.join(ROCM, "llvm", "bin", "clang++")
@@ -100,7 +103,15 @@ def build_hostsan(jobs: int = 8) -> str:
     return LIB_HOSTSAN
 
 
+def build_tests() -> str:
+    out = os.path.join(BUILD, "tests")
+    os.makedirs(out, exist_ok=True)
+    _link([_compile(TESTS_SRC, out, ["-I" + CSRC])], TESTS_LIB)
+    return TESTS_LIB
+
+
 if __name__ == "__main__":
     print(build())
+    print(build_tests())
     if len(sys.argv) > 1 and sys.argv[1] == "hostsan":
         print(build_hostsan())

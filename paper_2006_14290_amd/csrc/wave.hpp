@@ -173,35 +173,11 @@ __device__ __forceinline__ T exchange(T v)
     else return dpp<kQuadXor1>(v, v);
 }
 
-// Wavefront sums of K <= 64 values at once: at each stride a lane keeps half
-// of the values it still holds and adds its partner's copies of them, so K
-// sums take about K exchanges instead of 6 K. Returns the sum of value *k
-// (*k may be K or more where K is not a power of two: nothing then).
-template <int K, int Stride = 32, typename T>
-__device__ __forceinline__ T wave_sum_many(const T (&v)[K], int *k)
-{
-    if constexpr (K == 1) {
-        T t = v[0] + exchange<Stride>(v[0]);
-        if constexpr (Stride > 1) {
-            const T one[1] = {t};
-            return wave_sum_many<1, Stride / 2>(one, k);
-        }
-        return t;
-    } else {
-        constexpr int kHalf = (K + 1) / 2;
-        const bool hi = (lane_id() & Stride) != 0;
-        T t[kHalf];
-#pragma unroll
-        for (int i = 0; i < kHalf; ++i) {
-            const T b = i + kHalf < K ? v[i + kHalf < K ? i + kHalf : 0] : T(0);
-            const T keep = hi ? b : v[i], send = hi ? v[i] : b;
-            t[i] = keep + exchange<Stride>(send);
-        }
-        if (hi) *k += kHalf;
-        if constexpr (Stride > 1) return wave_sum_many<kHalf, Stride / 2>(t, k);
-        else return t[0];
-    }
-}
+}  // namespace spx
+
+#include "wave_many.hpp"
+
+namespace spx {
 
 // Inclusive segmented sum across the 64 lanes of a wavefront. A segment
 // starts at every lane whose head flag is set (and at lane 0). Hillis-Steele
