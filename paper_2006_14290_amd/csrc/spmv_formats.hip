@@ -60,20 +60,12 @@ __global__ __launch_bounds__(256) void scale_kernel(int64_t n, X *__restrict__ y
     if (i < n) y[i] = scaled(y[i], beta);
 }
 
-// Complete segment (row r, sum) of chunk [c0, c1): atomics if it may share
-// its row with a neighbouring chunk. row_before / row_after are the rows of
-// the entries just outside the chunk (-1 if none).
-// kBetaZero: beta == 0, so y is written without being read (no dependent
-// load in the tile loop).
+// The sum of row r, which lies inside one span. kBetaZero: beta == 0, so y is
+// written without being read (no dependent load in the tile loop).
 template <typename X, bool kAccumulate, bool kBetaZero>
-__device__ __forceinline__ void coo_write(int32_t r, X sum, bool chunk_start_seg, bool chunk_end_seg,
-                                          int32_t row_before, int32_t row_after, X *__restrict__ y, X alpha, X beta)
+__device__ __forceinline__ void coo_write(int32_t r, X sum, X *__restrict__ y, X alpha, X beta)
 {
-    const bool left = chunk_start_seg && row_before == r;
-    const bool right = chunk_end_seg && row_after == r;
-    if (left || right) {
-        unsafeAtomicAdd(y + r, alpha * sum);
-    } else if (kAccumulate) {
+    if (kAccumulate) {
         y[r] += alpha * sum;
     } else if (kBetaZero) {
         y[r] = alpha * sum;
@@ -82,13 +74,15 @@ __device__ __forceinline__ void coo_write(int32_t r, X sum, bool chunk_start_seg
     }
 }
 
-// What bounds it: on scattered columns the gathers that miss the L2 caches (x
-// of 8 MB against 4 MB per XCD: 153 million gathers and the stream make 91
-// million 128-byte fills, 11.6 GB in 1.54 ms, 7.5 TB/s); on stencils the scan of short segments
-// (7-point 160^3 float64 134 us, before 143).
+// What bounds it: the gathers on scattered columns, the scan of short segments
+// on stencils. The first row's atomic add waits for the span's end: issued
+// where the row closes it held up every later load of the span. Random rows of
+// 5 to 45 entries, 400,000 rows, float64 88.7 -> 62.2 us (rows that never
+// cross a span: 57.4 either way), 7-point 160^3 135 -> 118, 27-point 100^3
+// 121 -> 102.
 // 8 tiles: three wavefronts per SIMD (the loads in flight are enough, and
-// fewer rows' gathers share the L2 caches): float32 above 1008 -> 980 us,
-// 300,000 Zipf rows float64 331 -> 327; on stencils with 4 tiles it loses 20 %.
+// fewer rows' gathers share the L2 caches): Zipf rows, 153 million entries,
+// float32 1008 -> 980 us; on stencils with 4 tiles it loses 20 %.
 // kTogether: a chunk's gathers go out together; otherwise tile by tile.
 template <typename V, typename X, bool kAccumulate, bool kBetaZero, int kCooTiles, bool kTogether>
 __global__ __launch_bounds__(kCooThreads)
@@ -107,7 +101,8 @@ void coo_spmv_kernel(int32_t nrows, int64_t nnz, int64_t nspans,
     if (w >= nspans) return;
     // this wavefront's span [s0, s1): consecutive chunks of kCooChunk entries
     // whose open row is carried from chunk to chunk in registers; only rows
-    // crossing the span's ends need atomics
+    // crossing the span's ends need atomics, and those wait for the span's
+    // end: loads wait for every atomic issued before them
     const int64_t s0 = w * span;
     const int64_t s1 = (s0 + span < nnz) ? s0 + span : nnz;
     const int32_t row_before = s0 > 0 ? row[s0 - 1] : -1;
@@ -115,7 +110,9 @@ void coo_spmv_kernel(int32_t nrows, int64_t nnz, int64_t nspans,
 
     int32_t carry_row = -1;
     X carry_val = X(0);
-    bool carry_start = false;  // carried segment began at the span start
+    bool open_left = false;  // the span's first row began before it and has not closed yet
+    bool first_pending = false;
+    X first_val = X(0);  // its sum, once closed
     for (int64_t c0 = s0; c0 < s1; c0 += kCooChunk) {
         const int64_t c1 = (c0 + kCooChunk < s1) ? c0 + kCooChunk : s1;
         // issue every load of the chunk first (memory-level parallelism); the
@@ -161,12 +158,16 @@ void coo_spmv_kernel(int32_t nrows, int64_t nnz, int64_t nspans,
             const bool valid = e < c1;
             const int32_t rr = r[t];
             const int32_t r0 = readlane(rr, 0);
-            const bool span_first = (c0 == s0) && t == 0;
+            if (c0 == s0 && t == 0) open_left = r0 == row_before;
             // the carried segment ends before this tile: write it
             if (carry_row >= 0 && r0 != carry_row) {
-                if (lane == 0)
-                    coo_write<X, kAccumulate, kBetaZero>(carry_row, carry_val, carry_start, false, row_before,
-                                                         row_after, y, alpha, beta);
+                if (open_left) {
+                    first_val = carry_val;
+                    first_pending = true;
+                    open_left = false;
+                } else if (lane == 0) {
+                    coo_write<X, kAccumulate, kBetaZero>(carry_row, carry_val, y, alpha, beta);
+                }
                 carry_row = -1;
             }
             const bool merged = (carry_row >= 0);  // lane 0 continues the carried segment
@@ -183,25 +184,30 @@ void coo_spmv_kernel(int32_t nrows, int64_t nnz, int64_t nspans,
             const X sv = wave_segscan(v, head);
             // the last valid lane of the tile and the segment it closes are carried on
             const int tail_e = (c1 - tb < kWave) ? (int)(c1 - tb - 1) : kWave - 1;
-            const lane_mask_t heads = ballot64(head && lane > 0);
-            const lane_mask_t upto_me = (lane == kWave - 1) ? ~0ull : ((2ull << lane) - 1);
-            const bool seg0 = (heads & upto_me & ~1ull) == 0;  // my segment holds lane 0
-            const bool start_seg = seg0 && (span_first || (merged && carry_start));
             // a lane closes a segment when the next lane starts a new one
             const int32_t rn = wave_shift_down1(rr, -2);
-            if (lane < tail_e && rn != rr)
-                coo_write<X, kAccumulate, kBetaZero>(rr, sv, start_seg, false, row_before, row_after, y, alpha,
-                                                     beta);
+            bool closes = lane < tail_e && rn != rr;
+            if (open_left) {
+                const lane_mask_t m = ballot64(closes);
+                if (m != 0) {
+                    const int src = __builtin_ctzll(m);
+                    first_val = readlane(sv, src);
+                    first_pending = true;
+                    open_left = false;
+                    closes = closes && lane != src;
+                }
+            }
+            if (closes) coo_write<X, kAccumulate, kBetaZero>(rr, sv, y, alpha, beta);
             carry_row = readlane(rr, tail_e);
             carry_val = readlane(sv, tail_e);
-            const lane_mask_t upto_tail = (tail_e == kWave - 1) ? ~0ull : ((2ull << tail_e) - 1);
-            const bool last_seg_has_lane0 = (heads & upto_tail & ~1ull) == 0;
-            carry_start = last_seg_has_lane0 && (span_first || (merged && carry_start));
         }
     }
-    if (carry_row >= 0 && lane == 0)
-        coo_write<X, kAccumulate, kBetaZero>(carry_row, carry_val, carry_start, true, row_before, row_after, y, alpha,
-                                             beta);
+    if (lane != 0) return;
+    if (carry_row >= 0) {
+        if (open_left || carry_row == row_after) unsafeAtomicAdd(y + carry_row, alpha * carry_val);
+        else coo_write<X, kAccumulate, kBetaZero>(carry_row, carry_val, y, alpha, beta);
+    }
+    if (first_pending) unsafeAtomicAdd(y + row_before, alpha * first_val);
 }
 
 // One thread per kR consecutive rows (kR = 2 loads the two rows' slots as
