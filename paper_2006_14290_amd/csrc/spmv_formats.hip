@@ -210,21 +210,147 @@ void coo_spmv_kernel(int32_t nrows, int64_t nnz, int64_t nspans,
     if (first_pending) unsafeAtomicAdd(y + row_before, alpha * first_val);
 }
 
+// How the ELL product takes the gathers of x (the rule: ell_mode).
+enum EllMode : int {
+    kEllTogether = 0,  // those of kEllSlots slot columns in flight together
+    kEllByRows = 1,    // apart where a wavefront's rows are scattered, else together
+    kEllApart = 2      // one of a wavefront in flight at a time
+};
+
+// Slots [k, k + kEllSlots) of rows i .. i + kR - 1: columns (-1: no entry) and values.
+template <typename V, int kR>
+struct EllSlots {
+    typedef int32_t CR __attribute__((ext_vector_type(kR)));
+    typedef V VR __attribute__((ext_vector_type(kR)));
+    CR c[kEllSlots];
+    VR v[kEllSlots];
+
+    __device__ __forceinline__ void load(int32_t nrows, int32_t K, int64_t ld, int64_t i, int32_t k,
+                                         const int32_t *__restrict__ ecol, const V *__restrict__ eval)
+    {
+#pragma unroll
+        for (int u = 0; u < kEllSlots; ++u) {
+            if (k + u >= K) break;
+            const int64_t q = (int64_t)(k + u) * ld + (i < nrows ? i : 0);
+            c[u] = ld_stream(reinterpret_cast<const CR *>(ecol + q));
+            v[u] = ld_stream(reinterpret_cast<const VR *>(eval + q));
+        }
+    }
+    // Drops what lies outside the matrix; false: every row of the wavefront
+    // is into its padding.
+    __device__ __forceinline__ bool live(int32_t nrows, int32_t K, int64_t i, int32_t k)
+    {
+        bool any = false;
+#pragma unroll
+        for (int u = 0; u < kEllSlots; ++u)
+#pragma unroll
+            for (int r = 0; r < kR; ++r) {
+                if (!(k + u < K && i + r < nrows)) c[u][r] = -1;
+                if (u == kEllSlots - 1) any |= c[u][r] >= 0;
+            }
+        return ballot64(any) != 0;
+    }
+};
+
+// Whether the wavefront's rows have unrelated columns: fewer than a quarter of
+// them have their second entry (column c, -1: none) within 16 columns of that
+// of the row before.
+__device__ __forceinline__ bool scattered_rows(int32_t c)
+{
+    const int32_t before = wave_shift_up1(c, -1), d = c - before;
+    return __popcll(ballot64(c >= 0 && before >= 0 && d <= 16 && d >= -16)) < kWave / 4;
+}
+
+// The row sums, kEllSlots slot columns' gathers in flight together (under the
+// branch of its use a gather would be waited for alone). The next slots are
+// loaded kAhead = 0: after them, 1: before them, once some row is known to
+// have more, 2: before this block's columns are known. s: the first slots,
+// loaded.
+template <int kAhead, typename V, typename X, int kR>
+__device__ __forceinline__ void ell_together(EllSlots<V, kR> &s, int32_t nrows, int32_t K, int64_t ld, int64_t i,
+                                             const int32_t *__restrict__ ecol, const V *__restrict__ eval,
+                                             const X *__restrict__ x, X (&sum)[kR])
+{
+    EllSlots<V, kR> next;
+    for (int32_t k = 0;; k += kEllSlots) {
+        bool more = k + kEllSlots < K;
+        if (kAhead == 2 && more) next.load(nrows, K, ld, i, k + kEllSlots, ecol, eval);
+        const bool live = s.live(nrows, K, i, k);
+        more = more && live;
+        if (kAhead == 1 && more) next.load(nrows, K, ld, i, k + kEllSlots, ecol, eval);
+        X xv[kEllSlots][kR];
+#pragma unroll
+        for (int u = 0; u < kEllSlots; ++u)
+#pragma unroll
+            for (int r = 0; r < kR; ++r) {
+                xv[u][r] = X(0);
+                if (s.c[u][r] >= 0) xv[u][r] = x[s.c[u][r]];
+            }
+#pragma unroll
+        for (int u = 0; u < kEllSlots; ++u)
+#pragma unroll
+            for (int r = 0; r < kR; ++r)
+                if (s.c[u][r] >= 0) sum[r] += widen(s.v[u][r]) * xv[u][r];
+        if (!more) return;
+        if (kAhead == 0) s.load(nrows, K, ld, i, k + kEllSlots, ecol, eval);
+        else s = next;
+    }
+}
+
+// The same sums with one gather of a wavefront in flight at a time, the loads
+// of four slot columns before them.
+template <typename V, typename X, int kR>
+__device__ __forceinline__ void ell_apart(int32_t nrows, int32_t K, int64_t ld, int64_t i,
+                                          const int32_t *__restrict__ ecol, const V *__restrict__ eval,
+                                          const X *__restrict__ x, X (&sum)[kR])
+{
+    typedef typename EllSlots<V, kR>::CR CR;
+    typedef typename EllSlots<V, kR>::VR VR;
+    const bool in = i < nrows;
+    constexpr int U = kEllSlots;
+    for (int k = 0; k < K; k += U) {
+        CR c[U];
+        VR v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int r = 0; r < kR; ++r) {
+                c[u][r] = -1;
+                v[u][r] = V(0);
+            }
+            if (in && k + u < K) {
+                const int64_t q = (int64_t)(k + u) * ld + i;
+                c[u] = ld_stream(reinterpret_cast<const CR *>(ecol + q));
+                v[u] = ld_stream(reinterpret_cast<const VR *>(eval + q));
+#pragma unroll
+                for (int r = 1; r < kR; ++r)
+                    if (i + r >= nrows) c[u][r] = -1;  // a slot past the last row is not the matrix's
+            }
+        }
+        bool live = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int r = 0; r < kR; ++r)
+                if (c[u][r] >= 0) sum[r] += widen(v[u][r]) * x[c[u][r]];
+#pragma unroll
+        for (int r = 0; r < kR; ++r) live |= c[U - 1][r] >= 0;
+        if (ballot64(live) == 0) break;  // every row of the wavefront is into its padding
+    }
+}
+
 // One thread per kR consecutive rows (kR = 2 loads the two rows' slots as
-// one vector when ld is even and the arrays are aligned), kEllSlots slot
-// columns gathered together while the next ones are loaded; a wavefront stops
+// one vector when ld is even and the arrays are aligned); a wavefront stops
 // once all its rows are into their padding.
-// What bounds it: the slot stream; a gather under the same branch as its use
-// is waited for alone, so the gathers of a block come before its sums. Before
-// -> after, one MI355X, cold matrices: 7-point 160^3 binary16 45.4 -> 40.1 us,
-// float64 161^3 83.0 -> 79.6 (4.9 TB/s), 27-point 100^3 float32 44.8 -> 38.1
-// (5.9 TB/s), 64^2 grid 4.9 -> 3.8 us. Six and eight slot columns: 27-point float64 69.0
-// and 70.5 us against 67.1.
+// What bounds it: the slot stream on banded matrices, there 4.9 to 5.9 TB/s;
+// where the columns are scattered, the gathers. kEllByRows, float32: pairs
+// where the rows are scattered, otherwise one row per lane in kR passes (a
+// pair's gathers share lines).
 // kEpi: 0 = plain product; 1 = also the block's sum of y_i*w_i; 2 = that and
 // the sum of y_i^2 (one partial per work-group, reduced later in a fixed
 // order; a set solver flag skips the launch).
-template <typename V, typename X, int kEpi, int kR>
-__global__ __launch_bounds__(kEllThreads) void ell_spmv_kernel(int32_t nrows, int32_t K, int64_t ld,
+template <typename V, typename X, int kEpi, int kR, EllMode kMode>
+__global__ __launch_bounds__(kEllThreads, kMode == kEllByRows ? 8 : 1) void ell_spmv_kernel(int32_t nrows, int32_t K, int64_t ld,
                                                                int64_t grid_padded, const int32_t *__restrict__ ecol,
                                                                const V *__restrict__ eval, const X *__restrict__ x,
                                                                X *__restrict__ y, X alpha, X beta,
@@ -232,62 +358,57 @@ __global__ __launch_bounds__(kEllThreads) void ell_spmv_kernel(int32_t nrows, in
                                                                X *__restrict__ partials, const KState *st)
 {
     if (st != nullptr && st->flag != kRunning) return;
-    typedef int32_t CR __attribute__((ext_vector_type(kR)));
-    typedef V VR __attribute__((ext_vector_type(kR)));
     const int64_t nblocks = ((int64_t)nrows + kEllThreads * kR - 1) / (kEllThreads * kR);
     const int64_t blk = xcd_remap(blockIdx.x, grid_padded);
     if (blk >= nblocks) return;
     const int64_t i0 = (blk * kEllThreads + threadIdx.x) * kR;
-    const bool in = i0 < nrows;
     X sum[kR];
 #pragma unroll
     for (int r = 0; r < kR; ++r) sum[r] = X(0);
-    if (K > 0) {
-        constexpr int U = kEllSlots;
-        // slots [k, k + U) of the thread's rows
-        auto load = [&](int k, CR(&c)[U], VR(&v)[U]) {
+    int64_t row[kR];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (k + u >= K) break;
-                const int64_t q = (int64_t)(k + u) * ld + (in ? i0 : 0);
-                c[u] = ld_stream(reinterpret_cast<const CR *>(ecol + q));
-                v[u] = ld_stream(reinterpret_cast<const VR *>(eval + q));
+    for (int r = 0; r < kR; ++r) row[r] = i0 + r;
+    if constexpr (kMode == kEllApart) {
+        ell_apart(nrows, K, ld, i0, ecol, eval, x, sum);
+    } else if (K > 0) {
+        // binary16: the test reads the first slots themselves (a load before
+        // them costs a 27-point product 3 %); wider ones hold too many
+        // registers across it
+        constexpr bool kFirst = kMode == kEllTogether || sizeof(V) == 2;
+        EllSlots<V, kR> s;
+        bool apart = false;
+        if constexpr (kFirst) s.load(nrows, K, ld, i0, 0, ecol, eval);
+        if constexpr (kMode == kEllByRows) {
+            int32_t c = -1;  // of the second slot
+            if constexpr (kFirst) {
+                if (K > 1) c = s.c[1][0];
+            } else {
+                if (K > 1 && i0 < nrows) c = ecol[ld + i0];
             }
-        };
-        CR cc[U], cn[U];
-        VR vv[U], vn[U];
-        load(0, cc, vv);
-        for (int k = 0;; k += U) {
-            const bool more = k + U < K;
-            if (more) load(k + U, cn, vn);  // on their way while this block's gathers are
-            X xv[U][kR];
-            bool live = false;
+            apart = scattered_rows(c);
+        }
+        if (apart) {
+            ell_apart(nrows, K, ld, i0, ecol, eval, x, sum);
+        } else if constexpr (kMode == kEllByRows && kR > 1 && sizeof(V) == sizeof(float)) {
+            const int64_t wave0 = (blk * kEllThreads + (threadIdx.x & ~(kWave - 1))) * kR;
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int r = 0; r < kR; ++r) {
-                    if (!(in && k + u < K && i0 + r < nrows)) cc[u][r] = -1;
-                    xv[u][r] = X(0);
-                    if (cc[u][r] >= 0) xv[u][r] = x[cc[u][r]];
-                    if (u == U - 1) live |= cc[u][r] >= 0;
-                }
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int r = 0; r < kR; ++r)
-                    if (cc[u][r] >= 0) sum[r] += widen(vv[u][r]) * xv[u][r];
-            if (!more || ballot64(live) == 0) break;  // or every row of the wavefront is into its padding
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                cc[u] = cn[u];
-                vv[u] = vn[u];
+            for (int r = 0; r < kR; ++r) {
+                EllSlots<V, 1> t;
+                X one[1] = {X(0)};
+                row[r] = wave0 + r * kWave + lane_id();
+                t.load(nrows, K, ld, row[r], 0, ecol, eval);
+                ell_together<0>(t, nrows, K, ld, row[r], ecol, eval, x, one);
+                sum[r] = one[0];
             }
+        } else {
+            if constexpr (!kFirst) s.load(nrows, K, ld, i0, 0, ecol, eval);
+            ell_together<kMode == kEllTogether ? 2 : (kFirst ? 1 : 0)>(s, nrows, K, ld, i0, ecol, eval, x, sum);
         }
     }
     X d1 = X(0), d2 = X(0);
 #pragma unroll
     for (int r = 0; r < kR; ++r) {
-        const int64_t i = i0 + r;
+        const int64_t i = row[r];
         if (i < nrows) {
             X out = alpha * sum[r];
             if (beta != X(0)) out += beta * y[i];  // y is not read when beta == 0
@@ -358,11 +479,32 @@ spx_status coo_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X bet
                                  beta, stream);
 }
 
+// Up to kEllLargeRows rows (two work-groups of pairs per CU) the gathers of a
+// few wavefronts have to go out together. Above, where the columns are
+// scattered, one in flight per wavefront is better: all wavefronts walk the
+// rows' sorted entries side by side, and the window of x they share stays
+// small (900,000 rows of 16 random columns: 3.0 million L2 misses, 5.4 with
+// four slot columns together). Rows of 5 to 45 random entries, float64, apart
+// / together: 250,000 rows 43.6 / 39.2 us, 400,000 rows 55.3 / 71.5, 900,000
+// rows 141 / 155; 16 per row, 400,000 rows 39.7 / 47.6. Banded rows want them
+// together at any size (7-point 160^3 float64 74 / 70, float32 52 / 45,
+// binary16 45 / 40). Ragged rows (less than half of the slots stored) are
+// taken as scattered; otherwise every wavefront looks at its own rows, but for
+// binary16 rows of fewer than 8 entries, too short to pay for it.
+constexpr int32_t kEllLargeRows = 1 << 18;
+static EllMode ell_mode(const spx_matrix &A)
+{
+    if (A.nrows <= kEllLargeRows) return kEllTogether;
+    const int64_t stored = A.fmt == SPX_HYB ? A.nnz - A.coo_nnz : A.nnz;
+    if (2 * stored < (int64_t)A.ell_width * A.nrows) return kEllApart;
+    return A.val_type == SPX_F16 && A.ell_width < 8 ? kEllTogether : kEllByRows;
+}
+
 // Two rows per thread when the slot columns can be read two rows at a time:
 // even leading dimension (so a pair never straddles a slot column; with an
 // odd nrows the last pair's second row is in-bounds padding) and arrays
-// aligned to two entries. Not float32: a pair's gathers share lines and go out
-// together, and the float32 stream is better off with one row per lane.
+// aligned to two entries. Float32 gathered together takes one row per lane: a
+// pair's gathers share lines, and the stream is better off without.
 // Pairs against single rows, cold: 27-point 100^3 float64 61.5 / 62.6 us,
 // float32 50.2 / 38.1, binary16 36.4 / 41.6; 7-point 160^3 float64 70.8 / 70.7,
 // float32 50.2 / 44.6, binary16 40.2 / 49.2.
@@ -372,7 +514,7 @@ static int ell_rows_per_thread(const spx_matrix &A)
     const bool even = (A.ell_ld % 2) == 0;
     const bool aligned = (reinterpret_cast<uintptr_t>(A.ell_col) % 8 == 0) &&
                          (reinterpret_cast<uintptr_t>(A.ell_val) % (2 * sv) == 0);
-    return even && aligned && A.val_type != SPX_F32 ? 2 : 1;
+    return even && aligned && (A.val_type != SPX_F32 || ell_mode(A) != kEllTogether) ? 2 : 1;
 }
 
 int64_t ell_dot_parts(const spx_matrix &A)
@@ -388,18 +530,25 @@ spx_status ell_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X bet
     const int64_t blocks = ceil_div(A.nrows, (int64_t)kEllThreads * kr);
     const int64_t grid = pad_to_xcds(blocks);
 #define SPX_ELL_LAUNCH(E, R)                                                                                        \
-    ell_spmv_kernel<V, X, E, R><<<(unsigned)grid, kEllThreads, 0, stream>>>(                                        \
+    switch (ell_mode(A)) {                                                                                          \
+    case kEllTogether: SPX_ELL_KERNEL(E, R, kEllTogether); break;                                                   \
+    case kEllByRows: SPX_ELL_KERNEL(E, R, kEllByRows); break;                                                       \
+    default: SPX_ELL_KERNEL(E, R, kEllApart); break;                                                                \
+    }
+#define SPX_ELL_KERNEL(E, R, L)                                                                                     \
+    ell_spmv_kernel<V, X, E, R, L><<<(unsigned)grid, kEllThreads, 0, stream>>>(                                        \
         A.nrows, A.ell_width, A.ell_ld, grid, A.ell_col, static_cast<const V *>(A.ell_val), x, y, alpha, beta,      \
         dot_with, partials, st)
     if (kr == 2) {
-        if (epi == 2) SPX_ELL_LAUNCH(2, 2);
-        else if (epi == 1) SPX_ELL_LAUNCH(1, 2);
-        else SPX_ELL_LAUNCH(0, 2);
+        if (epi == 2) { SPX_ELL_LAUNCH(2, 2) }
+        else if (epi == 1) { SPX_ELL_LAUNCH(1, 2) }
+        else { SPX_ELL_LAUNCH(0, 2) }
     } else {
-        if (epi == 2) SPX_ELL_LAUNCH(2, 1);
-        else if (epi == 1) SPX_ELL_LAUNCH(1, 1);
-        else SPX_ELL_LAUNCH(0, 1);
+        if (epi == 2) { SPX_ELL_LAUNCH(2, 1) }
+        else if (epi == 1) { SPX_ELL_LAUNCH(1, 1) }
+        else { SPX_ELL_LAUNCH(0, 1) }
     }
+#undef SPX_ELL_KERNEL
 #undef SPX_ELL_LAUNCH
     SPX_LAUNCHED();
     return SPX_OK;

@@ -48,3 +48,8 @@ def ragged():
 def test_coo_rows_across_spans(ragged):
     # 1.4 times the CSR product; 2.0 with the atomics ahead of a span's loads
     assert ragged(spx.COO) < 1.7
+
+
+def test_ell_random_rows(ragged):
+    # 1.27 times the CSR product; 1.64 with the gathers of four slot columns together
+    assert ragged(spx.ELL) < 1.45
