@@ -571,7 +571,9 @@ spx_status hyb_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X bet
 // the row at k * C): kSellSlots columns at a time, the next ones loaded while
 // this block's gathers are in flight. Columns past the last are read again
 // and dropped; the entries are added in order.
-template <typename V, typename X>
+// kByRows (64-row slices, step 1): a wavefront of scattered rows takes one
+// gather at a time instead.
+template <bool kByRows, typename V, typename X>
 __device__ __forceinline__ X slot_sum(const int32_t *__restrict__ cs, const V *__restrict__ vs, int32_t k,
                                       int32_t step, int32_t w, int32_t C, const X *__restrict__ x)
 {
@@ -589,6 +591,16 @@ __device__ __forceinline__ X slot_sum(const int32_t *__restrict__ cs, const V *_
     int32_t cc[U], cn[U];
     V vv[U], vn[U];
     load(k, cc, vv);
+    if (kByRows && scattered_rows(cc[1])) {
+        while (true) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k + u * step < w && cc[u] >= 0) sum += widen(vv[u]) * x[cc[u]];
+            k += U * step;
+            if (k >= w) return sum;
+            load(k, cc, vv);
+        }
+    }
     while (true) {
         const int32_t next = k + U * step;
         if (next < w) load(next, cn, vn);
@@ -640,7 +652,7 @@ __global__ __launch_bounds__(kSellThreads) void sellp_spmv_kernel(int32_t nrows,
     const int32_t k0 = sets[s], w = sets[s + 1] - k0;
     const int32_t *__restrict__ cs = scol + (int64_t)k0 * C + l;
     const V *__restrict__ vs = sval + (int64_t)k0 * C + l;
-    const X sum = slot_sum(cs, vs, g, G, w, C, x);
+    const X sum = slot_sum<false>(cs, vs, g, G, w, C, x);
     part[tid] = sum;
     __syncthreads();
     const int64_t row = s * C + l;
@@ -663,10 +675,10 @@ __global__ __launch_bounds__(kSellThreads) void sellp_spmv_kernel(int32_t nrows,
     }
 }
 
-// SELL-P with 64-row slices: one wavefront per slice, one lane per row, four
+// SELL-P with 64-row slices: one wavefront per slice, one lane per row, eight
 // slot columns in flight per lane (the slot columns are read coalesced and,
 // on banded matrices, so are the gathers of x); no cross-lane reduction.
-template <typename V, typename X, int kEpi>
+template <typename V, typename X, int kEpi, bool kByRows>
 __global__ __launch_bounds__(kSellThreads) void sellp64_spmv_kernel(int32_t nrows, int64_t nslices,
                                                                    int64_t grid_padded,
                                                                    const int32_t *__restrict__ sets,
@@ -688,7 +700,7 @@ __global__ __launch_bounds__(kSellThreads) void sellp64_spmv_kernel(int32_t nrow
         const int32_t k0 = sets[s], w = sets[s + 1] - k0;
         const int32_t *__restrict__ cs = scol + (int64_t)k0 * kWave + l;
         const V *__restrict__ vs = sval + (int64_t)k0 * kWave + l;
-        const X sum = slot_sum(cs, vs, 0, 1, w, kWave, x);
+        const X sum = slot_sum<kByRows>(cs, vs, 0, 1, w, kWave, x);
         const int64_t row = s * kWave + l;
         if (row < nrows) {
             X out = alpha * sum;
@@ -707,6 +719,22 @@ __global__ __launch_bounds__(kSellThreads) void sellp64_spmv_kernel(int32_t nrow
     }
 }
 
+// Whether the 64-row slices' wavefronts look for scattered rows (see ell_mode
+// for why these are better off with one gather at a time). It pays where the
+// rows fill one to two wavefronts per SIMD (rows of 32 random columns,
+// 100,000 rows: float64 19.5 us against 24.4 together, float32 13.9 against
+// 19.0; 50,000 rows 9.9 together; 24 per row, 200,000 rows, float32 33.7 and
+// 31.1), and in float64 where x is larger than one
+// XCD's L2 (rows of 5 to 45 random entries, 900,000 rows: 146.6 against 153;
+// 400,000 rows 64.2 against 63.2). Slices of fewer than 8 slot columns are too
+// short to pay for the look (5-point 1500^2: 37.7 us against 33.9).
+static bool sell_by_rows(const spx_matrix &A)
+{
+    if (A.slice_cols * kWave < int64_t(8) * A.nrows) return false;
+    return (A.nrows > (1 << 16) && A.nrows <= (1 << 17)) ||
+           (A.val_type == SPX_F64 && A.ncols * (int64_t)sizeof(double) > kCooCachedX);
+}
+
 int64_t sellp_dot_parts(const spx_matrix &A)
 {
     const int64_t ns = A.nrows > 0 ? ceil_div(A.nrows, A.slice_size) : 1;
@@ -722,13 +750,19 @@ spx_status sellp_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X b
     if (C == kWave) {
         const int64_t nblocks = sellp_dot_parts(A);
         const int64_t grid = pad_to_xcds(nblocks);
-#define SPX_SELL64_LAUNCH(E)                                                                                       \
-    sellp64_spmv_kernel<V, X, E><<<(unsigned)grid, kSellThreads, 0, stream>>>(                                     \
+#define SPX_SELL64_LAUNCH(E, B)                                                                                    \
+    sellp64_spmv_kernel<V, X, E, B><<<(unsigned)grid, kSellThreads, 0, stream>>>(                                  \
         A.nrows, ns, grid, A.slice_sets, A.ell_col, static_cast<const V *>(A.ell_val), x, y, alpha, beta, dot_with, \
         partials, st)
-        if (epi == 2) SPX_SELL64_LAUNCH(2);
-        else if (epi == 1) SPX_SELL64_LAUNCH(1);
-        else SPX_SELL64_LAUNCH(0);
+        if (sell_by_rows(A)) {
+            if (epi == 2) SPX_SELL64_LAUNCH(2, true);
+            else if (epi == 1) SPX_SELL64_LAUNCH(1, true);
+            else SPX_SELL64_LAUNCH(0, true);
+        } else {
+            if (epi == 2) SPX_SELL64_LAUNCH(2, false);
+            else if (epi == 1) SPX_SELL64_LAUNCH(1, false);
+            else SPX_SELL64_LAUNCH(0, false);
+        }
 #undef SPX_SELL64_LAUNCH
         SPX_LAUNCHED();
         return SPX_OK;

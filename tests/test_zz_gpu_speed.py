@@ -53,3 +53,19 @@ def test_coo_rows_across_spans(ragged):
 def test_ell_random_rows(ragged):
     # 1.27 times the CSR product; 1.64 with the gathers of four slot columns together
     assert ragged(spx.ELL) < 1.45
+
+
+def test_sellp_random_rows():
+    """Rows of 48 random entries, 100,000 rows, against the ELL product."""
+    n, K = 100_000, 48
+    g = torch.Generator(device="cuda").manual_seed(1)
+    col = torch.arange(K, device="cuda") * (n // K) + torch.randint(0, n // K, (n, K), generator=g, device="cuda")
+    rowptr = (torch.arange(n + 1, device="cuda") * K).to(torch.int32)
+    val = torch.rand(n * K, generator=g, device="cuda", dtype=torch.float64)
+    A = spx.Matrix(spx.CSR, spx.F64, n, n, n * K, rowptr=rowptr, colidx=col.to(torch.int32).reshape(-1), vals=val)
+    x = torch.rand(n, dtype=torch.float64, device="cuda")
+    y, z, ell, sellp = torch.empty_like(x), torch.empty_like(x), spx.convert(A, spx.ELL), spx.convert(A, spx.SELLP)
+    t_ell, t = seconds(lambda: spx.spmv(ell, x, y), lambda: spx.spmv(sellp, x, z))
+    print(f"ELL {t_ell * 1e6:.1f} us, SELL-P {t * 1e6:.1f} us", flush=True)
+    # 1.0 times the ELL product; 1.66 with the gathers of eight slot columns together
+    assert t / t_ell < 1.35
