@@ -201,6 +201,11 @@ constexpr int kTpScanThreads = 1024;
 constexpr int kTpSortThreads = 512;               // of the one-segment sort
 constexpr int kTpSortWaves = kTpSortThreads / kWave;
 
+// A wavefront walks the rows of its entries 64 at a time; where more than this
+// many steps do not reach its last entry (runs of empty rows: fewer than one
+// entry in two rows), it searches for every entry's row instead. 1,000 entries
+// in 10 million rows: the transpose 47 ms walked, 93 us searched.
+constexpr int kTpRowSteps = 32;
 constexpr int kTpColBits = 22;
 static_assert((int64_t)kTpMaxBuckets * kTpMaxWidth == int64_t(1) << kTpColBits, "a column fits its bits");
 static_assert(kTpWaveTile <= 1 << (32 - kTpColBits), "and a wavefront's entries the rest");
@@ -406,6 +411,28 @@ __device__ __forceinline__ int32_t tp_scan_max(int32_t v)
     return v;
 }
 
+// The row of every entry of [e0, e1), each by its own bisection of
+// [first, nrows] (the last row that starts at or before it): all of a lane's
+// entries step by step together, so that a step costs one load's latency.
+__device__ void tp_find_rows(const int32_t *__restrict__ rowptr, int64_t first, int32_t nrows, int64_t e0, int64_t e1,
+                             int32_t *__restrict__ s_row)
+{
+    int32_t at[kTpItems];
+#pragma unroll
+    for (int u = 0; u < kTpItems; ++u) at[u] = (int32_t)first;
+    int64_t step = 1;
+    while (first + step < nrows) step *= 2;
+    for (; step > 0; step /= 2) {
+#pragma unroll
+        for (int u = 0; u < kTpItems; ++u) {
+            const int64_t e = e0 + u * kWave + lane_id(), r = at[u] + step;
+            if (r < nrows && e < e1 && rowptr[r] <= e) at[u] = (int32_t)r;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kTpItems; ++u) s_row[u * kWave + lane_id()] = at[u];
+}
+
 // Entries to their buckets, in order. T: unsigned integer of the value's width.
 template <typename T>
 __global__ __launch_bounds__(kTpThreads) void tp_partition_kernel(
@@ -436,13 +463,15 @@ __global__ __launch_bounds__(kTpThreads) void tp_partition_kernel(
         // mark where this stretch's rows start (of several rows that start at
         // one entry the last is the one that holds it)
         int32_t v;
-        int64_t r = lower_bound_wave(rowptr, 0, nrows, e0 + 1, &v) - 1 + lane;
-        while (true) {
+        const int64_t first = lower_bound_wave(rowptr, 0, nrows, e0 + 1, &v) - 1;
+        int64_t r = first + lane;
+        bool walked = false;
+        for (int step = 0; step < kTpRowSteps && !walked; ++step, r += kWave) {
             const int64_t start = r < nrows ? rowptr[r] : e1;
             if (start < e1) atomicMax(&s_row[w][start > e0 ? start - e0 : 0], (int32_t)r);
-            if (ballot64(start >= e1) != 0) break;
-            r += kWave;
+            walked = ballot64(start >= e1) != 0;
         }
+        if (!walked) tp_find_rows(rowptr, first, nrows, e0, e1, s_row[w]);
     }
     const lane_mask_t below = (lane_mask_t(1) << lane) - 1;
 #pragma unroll

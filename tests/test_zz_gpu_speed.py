@@ -51,7 +51,7 @@ def test_coo_rows_across_spans(ragged):
 
 
 def test_ell_random_rows(ragged):
-    # 1.27 times the CSR product; 1.64 with the gathers of four slot columns together
+    # 1.25 times the CSR product; 1.62 with the gathers of four slot columns together
     assert ragged(spx.ELL) < 1.45
 
 
@@ -69,3 +69,17 @@ def test_sellp_random_rows():
     print(f"ELL {t_ell * 1e6:.1f} us, SELL-P {t * 1e6:.1f} us", flush=True)
     # 1.0 times the ELL product; 1.66 with the gathers of eight slot columns together
     assert t / t_ell < 1.35
+
+
+def test_transpose_of_mostly_empty_rows():
+    """1,000 entries in 10 million rows against a copy of the row pointer."""
+    n, nnz = 10_000_000, 1000
+    rowptr = torch.searchsorted(torch.arange(nnz, device="cuda") * (n // nnz), torch.arange(n + 1, device="cuda"))
+    col = torch.randint(0, 5000, (nnz,), device="cuda", dtype=torch.int32)
+    A = spx.Matrix(spx.CSR, spx.F64, n, 5000, nnz, rowptr=rowptr.to(torch.int32), colidx=col,
+                   vals=torch.rand(nnz, dtype=torch.float64, device="cuda"))
+    to = torch.empty_like(A.rowptr)
+    t_copy, t = seconds(lambda: to.copy_(A.rowptr), lambda: spx.csr_transpose(A))
+    print(f"copy {t_copy * 1e6:.1f} us, transpose {t * 1e6:.1f} us", flush=True)
+    # 7 times the copy; every row walked by one wavefront took 3,600 times as long
+    assert t < 100 * t_copy
