@@ -16,9 +16,8 @@ constexpr int kVecChunk = kVecThreads * kVecItems;     // elements per work-grou
 
 inline int64_t vec_blocks(int64_t n) { return n > 0 ? ceil_div(n, kVecChunk) : 1; }
 
-// Partials written by the fused product + dot of A (CSR: one per tile;
-// SELL-P: one per slice; other formats: the separate dot kernel's blocks),
-// and the partials slots a solver needs (at least one vector pass).
+// Partials written by the fused product + dot of A (one per work-group of the
+// kernel that A takes; COO and HYB: the separate dot kernel's blocks).
 inline int64_t spmv_dot_parts(const spx_matrix &A)
 {
     if (A.fmt == SPX_CSR) return csr_dot_parts(A);
@@ -26,12 +25,17 @@ inline int64_t spmv_dot_parts(const spx_matrix &A)
     if (A.fmt == SPX_ELL) return ell_dot_parts(A);
     return vec_blocks(A.nrows);
 }
+
+// Partials slots a solver needs: those of a vector pass and of any kernel that
+// the product may take. The kernel depends on the row-length hint and on the
+// arrays' addresses as well; the slots do not, so that a workspace made for a
+// matrix before its hint was set, or at other addresses, is large enough.
 inline int64_t partial_slots(const spx_matrix &A)
 {
-    // (CSR: for whichever of its kernels the product may take)
-    int64_t a = spmv_dot_parts(A);
-    const int64_t b = vec_blocks(A.nrows), t = A.fmt == SPX_CSR ? csr_tiles(A.nnz) : 0;
-    if (t > a) a = t;
+    int64_t a = vec_blocks(A.nrows);
+    int64_t b = A.fmt == SPX_CSR ? csr_dot_parts_most(A.nrows, A.nnz) : 0;
+    if (A.fmt == SPX_ELL && A.nrows > 0) b = ceil_div(A.nrows, kEllThreads);
+    if (A.fmt == SPX_SELLP) b = sellp_dot_parts(A);
     return a > b ? a : b;
 }
 

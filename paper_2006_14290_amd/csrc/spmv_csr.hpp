@@ -30,6 +30,16 @@ struct KState;
 int csr_rows_sub(const spx_matrix &A);
 // Number of dot partials the CSR product with epi > 0 writes for A.
 int64_t csr_dot_parts(const spx_matrix &A);
+// The most that any of the CSR kernels writes for a matrix of this size: a
+// work-group takes 2048 entries (tiles) or, at most 2048 of them, 16 rows or
+// more (row-per-subwarp: up to kRowMaxRows rows; staged rows: a grid of up to
+// 1024).
+inline int64_t csr_dot_parts_most(int64_t nrows, int64_t nnz)
+{
+    const int64_t rows = pad_to_xcds(ceil_div(nrows, 16)), tiles = csr_tiles(nnz);
+    const int64_t most = rows < 2048 ? rows : 2048;
+    return most > tiles ? most : tiles;
+}
 
 // Writes the tile partition (2 * (csr_tiles(nnz) + 1) int32) of A.
 spx_status csr_partition_launch(const spx_matrix &A, int32_t *part, hipStream_t stream);
