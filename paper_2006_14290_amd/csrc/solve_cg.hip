@@ -46,7 +46,7 @@ __device__ __forceinline__ void cg_commit(const KState *in, KState *out, double 
 template <typename X>
 __global__ __launch_bounds__(kVecThreads) void cg_init_kernel(int64_t n, const X *__restrict__ b,
                                                              const X *__restrict__ q, const X *__restrict__ dinv,
-                                                             X *__restrict__ r, X *__restrict__ z, X *__restrict__ p,
+                                                             X *__restrict__ r, X *__restrict__ p,
                                                              X *__restrict__ partials, KState *st)
 {
     __shared__ X s_red[kVecThreads / kWave];
@@ -60,7 +60,6 @@ __global__ __launch_bounds__(kVecThreads) void cg_init_kernel(int64_t n, const X
             const X ri = q ? bi - q[i] : bi;
             const X zi = dinv ? ri * dinv[i] : ri;
             r[i] = ri;
-            if (dinv) z[i] = zi;
             p[i] = zi;
             bb += bi * bi;
             rz += ri * zi;
@@ -199,9 +198,8 @@ __global__ void cg_state_copy_kernel(const KState *__restrict__ in, KState *__re
 
 template <typename X>
 __global__ __launch_bounds__(kVecThreads) void cg_restart_kernel(int64_t n, const X *__restrict__ r,
-                                                                const X *__restrict__ dinv, X *__restrict__ z,
-                                                                X *__restrict__ p, X *__restrict__ partials,
-                                                                KState *st)
+                                                                const X *__restrict__ dinv, X *__restrict__ p,
+                                                                X *__restrict__ partials, KState *st)
 {
     __shared__ X s_red[kVecThreads / kWave];
     const int64_t base = (int64_t)blockIdx.x * kVecChunk;
@@ -212,7 +210,6 @@ __global__ __launch_bounds__(kVecThreads) void cg_restart_kernel(int64_t n, cons
         if (i < n) {
             const X ri = r[i];
             const X zi = dinv ? ri * dinv[i] : ri;
-            if (dinv) z[i] = zi;
             p[i] = zi;
             rz += ri * zi;
         }
@@ -230,7 +227,7 @@ __global__ void zero_kernel(int64_t n, X *__restrict__ x)
 
 template <typename V, typename X>
 struct CgBufs {
-    X *r, *z, *p, *q, *d, *dinv, *partials;
+    X *r, *z, *p, *q, *d, *dinv, *partials;  // z: block Jacobi only, else r
     double *inv;  // block-Jacobi inverse blocks
     KState *st;
     int32_t *part;
@@ -245,7 +242,7 @@ static CgBufs<V, X> cg_carve(Carve &c, const spx_matrix &A, int precond)
     w.r = c.take<X>(n);
     w.p = c.take<X>(n);
     w.q = c.take<X>(n);
-    w.z = precond ? c.take<X>(n) : w.r;
+    w.z = precond >= 2 ? c.take<X>(n) : w.r;
     w.d = precond == 1 ? c.take<X>(n) : nullptr;
     w.dinv = precond == 1 ? c.take<X>(n) : nullptr;
     w.inv = precond >= 2 ? c.take<double>(ceil_div(n, precond) * precond * precond) : nullptr;
@@ -349,10 +346,10 @@ spx_status cg_run(const spx_matrix &A_in, const X *b, X *x, const SolveSpec &sp,
     const unsigned gv = (unsigned)vec_blocks(n);
     if (sp.x0_zero) {
         zero_kernel<X><<<(unsigned)ceil_div(n, kVecThreads), kVecThreads, 0, s>>>(n, x);
-        cg_init_kernel<X><<<gv, kVecThreads, 0, s>>>(n, b, nullptr, w.dinv, w.r, w.z, w.p, w.partials, w.st);
+        cg_init_kernel<X><<<gv, kVecThreads, 0, s>>>(n, b, nullptr, w.dinv, w.r, w.p, w.partials, w.st);
     } else {
         SPX_CHECK(spmv_dispatch(A, x, w.q, 1.0, 0.0, s));
-        cg_init_kernel<X><<<gv, kVecThreads, 0, s>>>(n, b, w.q, w.dinv, w.r, w.z, w.p, w.partials, w.st);
+        cg_init_kernel<X><<<gv, kVecThreads, 0, s>>>(n, b, w.q, w.dinv, w.r, w.p, w.partials, w.st);
     }
     SPX_LAUNCHED();
     // block Jacobi: z = M^{-1} r, p = z and the r.z partials (row 1 of the init sums)
@@ -438,7 +435,7 @@ spx_status cg_run(const spx_matrix &A_in, const X *b, X *x, const SolveSpec &sp,
                 break;
             }
             // restart the recurrences from the true residual (already in r)
-            cg_restart_kernel<X><<<gv, kVecThreads, 0, s>>>(n, w.r, w.dinv, w.z, w.p, w.partials, w.st);
+            cg_restart_kernel<X><<<gv, kVecThreads, 0, s>>>(n, w.r, w.dinv, w.p, w.partials, w.st);
             SPX_LAUNCHED();
             if (bs) SPX_CHECK(bj_apply<X>(n, bs, w.inv, w.r, w.z, w.p, w.partials, 0, w.st, false, s));
             SPX_CHECK(launch_finish<X>(w.partials, gv, 1, w.st, kOpCgRestart, s));

@@ -54,3 +54,15 @@ def test_ell_addresses(lib, n, solver):  # noqa: F811
     got = {workspace(lib, solver, fmt=ELL, nrows=n, nnz=n * 7, ell_width=7, ell_ld=ld, ell_col=c, ell_val=v)
            for ld in (n, n + 1) for c, v in ((0x20000, 0x30000), (0x20004, 0x30000), (0x20000, 0x30008))}
     assert len(got) == 1, sorted(got)
+
+
+def test_cg_vectors(lib):  # noqa: F811
+    """Jacobi CG keeps the diagonal and its inverse besides plain CG's
+    vectors, block Jacobi z and the inverse blocks."""
+    n = 1 << 16  # a vector is a whole number of 256-byte pieces
+
+    def cg(precond):
+        return workspace(lib, 0, precond, fmt=CSR, nrows=n, nnz=7 * n, rowptr=0x10000, colidx=0x20000, vals=0x30000)
+
+    assert cg(1) - cg(0) == 2 * 8 * n
+    assert cg(2) - cg(0) == 3 * 8 * n
