@@ -461,8 +461,8 @@ __global__ __launch_bounds__(kTotalThreads) void slots_total_kernel(const int32_
 // Row i of the CSR result: the row's slots (slot order, padding dropped)
 // merged with its COO entries (if any), ascending by column. Wavefront w
 // counts and then places its part of the 64 rows' slots; COO entries that all
-// come after the slots (the canonical split) are copied row by row, others
-// are merged by one lane.
+// come after the slots (the canonical split: the first above every slot's
+// column) are copied row by row, others are merged by one lane.
 template <typename V>
 __global__ __launch_bounds__(kCvThreads) void slots_to_csr_kernel(
     const int32_t *__restrict__ ecol, const V *__restrict__ eval, int32_t n, SlotLayout lay,
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(kCvThreads) void slots_to_csr_kernel(
 {
     __shared__ int32_t s_col[kCvStageNnz];
     __shared__ V s_val[kCvStageNnz];
-    __shared__ int32_t s_cnt[kCvParts][kWave], s_last[kCvParts][kWave];
+    __shared__ int32_t s_cnt[kCvParts][kWave], s_last[kCvParts][kWave];  // last: largest column
     const int64_t r0 = (int64_t)blockIdx.x * kCvStageRows;
     const int lane = lane_id(), part = threadIdx.x / kWave;
     const int64_t i = r0 + lane;
@@ -507,14 +507,14 @@ __global__ __launch_bounds__(kCvThreads) void slots_to_csr_kernel(
     for (int u = 0; u < kCvChunk; ++u)
         if (c[u] >= 0) {
             ++cnt;
-            last = c[u];
+            last = c[u] > last ? c[u] : last;
         }
 #pragma unroll 8
     for (int32_t k = k0 + kCvChunk; k < k1; ++k) {
         const int32_t t = ecol[sr.base + k * sr.step];
         if (t >= 0) {
             ++cnt;
-            last = t;
+            last = t > last ? t : last;
         }
     }
     s_cnt[part][lane] = cnt;
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(kCvThreads) void slots_to_csr_kernel(
     for (int q = 0; q < kCvParts; ++q) {
         if (q < part) o += s_cnt[q][lane];
         ell_end += s_cnt[q][lane];
-        ell_last = s_last[q][lane] >= 0 ? s_last[q][lane] : ell_last;
+        ell_last = s_last[q][lane] > ell_last ? s_last[q][lane] : ell_last;
     }
     const bool after = cb >= ce || ccol[cb] > ell_last;  // no COO entry before a slot
     if (after) {
