@@ -48,12 +48,15 @@ constexpr int kWideStageForms = 5;   // rows of up to 8, 16, 32, 64, 128 entries
 constexpr int kWideRunTiles = 16;    // consecutive tiles on one XCD
 static_assert(kWideThreads == kCsrThreads, "both phases reduce with the same work-group");
 
-// 16 bytes per lane into LDS; see lds_copy16. Temporal: the solved systems'
+// kBytes per lane into LDS; see lds_copy16. Temporal: the solved systems'
 // matrices are read again every iteration and may stay in the Infinity Cache.
-__device__ __forceinline__ void wide_copy16(const void *g, void *lds)
+template <int kBytes>
+__device__ __forceinline__ void wide_copy(const void *g, void *lds)
 {
-    __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) const void *)g,
-                                     (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
+    auto *from = (__attribute__((address_space(1))) const void *)g;
+    auto *to = (__attribute__((address_space(3))) void *)lds;
+    if constexpr (kBytes == 16) __builtin_amdgcn_global_load_lds(from, to, 16, 0, 0);
+    else __builtin_amdgcn_global_load_lds(from, to, 4, 0, 0);
 }
 
 // Work-group sum in a fixed order (result in every thread).
@@ -97,7 +100,8 @@ __device__ double wide_longest_row(const WideSlot &S, int32_t r0, int32_t r1, do
 }
 
 // Product form of a system from its blocks' longest rows: the rule of the
-// single product's staged-rows kernel. len is the power of two at or above
+// single product's staged-rows kernel, but for the arrays' alignment: a
+// system's bits must not depend on where its arrays lie. len is the power of two at or above
 // the longest row; rows fill at least half of len on average, so that the
 // ceil(n * len / 4096) row blocks are never more than the ntiles tiles.
 // Returns 1 + log2(len / 8), or 0 for the tile form.
@@ -113,7 +117,6 @@ __device__ int16_t wide_stage_form(const WideSlot &S, const double *longest, dou
 #pragma unroll
     for (int w = 0; w < kWideWaves; ++w) m = fmax(m, s_red[w]);
     if (S.nnz < kStageMinNnz || S.nnz > INT32_MAX - kStageMinNnz) return 0;
-    if (((reinterpret_cast<uintptr_t>(S.col) | reinterpret_cast<uintptr_t>(S.val)) & 15) != 0) return 0;
     for (int f = 0; f < kWideStageForms; ++f) {
         const int64_t len = 8 << f;
         if (m <= (double)len) return 2 * S.nnz >= len * S.n ? (int16_t)(f + 1) : (int16_t)0;
@@ -125,6 +128,9 @@ __device__ int16_t wide_stage_form(const WideSlot &S, const double *longest, dou
 // [k * 512 >> sh, + 512 >> sh) with 1 << sh lanes per row, each wavefront two
 // blocks of 64 >> sh rows, the second one copied into LDS while the first
 // one's gathers are in flight. Tiles past the last row write zero partials.
+// kVec: 16-byte copies; arrays that these cannot read are copied 4 bytes per
+// lane, to the same places.
+template <bool kVec>
 __device__ __forceinline__ void wide_stage_tile(unsigned char *s_raw, double *s_red, int32_t k, const WideSlot &S,
                                                 int sh, const double *src, double *y, const double *dw)
 {
@@ -158,16 +164,30 @@ __device__ __forceinline__ void wide_stage_tile(unsigned char *s_raw, double *s_
             const int32_t a0 = s & ~3;
             const int32_t lim = e < nnz8 ? e : nnz8;
             const int32_t last = lim > 0 ? lim - 1 : 0;
-            const int32_t lastc = last & ~3, lastv = last & ~1;
+            if constexpr (kVec) {
+                const int32_t lastc = last & ~3, lastv = last & ~1;
 #pragma unroll
-            for (int u = 0; u < kCap / (4 * kWave); ++u) {
-                const int32_t p = a0 + (u * kWave + lane) * 4;
-                wide_copy16(S.col + (p < lastc ? p : lastc), s_col + u * kWave * 4);
-            }
+                for (int u = 0; u < kCap / (4 * kWave); ++u) {
+                    const int32_t p = a0 + (u * kWave + lane) * 4;
+                    wide_copy<16>(S.col + (p < lastc ? p : lastc), s_col + u * kWave * 4);
+                }
 #pragma unroll
-            for (int u = 0; u < kCap / (2 * kWave); ++u) {
-                const int32_t p = a0 + (u * kWave + lane) * 2;
-                wide_copy16(S.val + (p < lastv ? p : lastv), s_val + u * kWave * 2);
+                for (int u = 0; u < kCap / (2 * kWave); ++u) {
+                    const int32_t p = a0 + (u * kWave + lane) * 2;
+                    wide_copy<16>(S.val + (p < lastv ? p : lastv), s_val + u * kWave * 2);
+                }
+            } else {
+#pragma unroll 1
+                for (int u = 0; u < kCap / kWave; ++u) {
+                    const int32_t p = a0 + u * kWave + lane;
+                    wide_copy<4>(S.col + (p < last ? p : last), s_col + u * kWave);
+                }
+                const int32_t *words = reinterpret_cast<const int32_t *>(S.val);  // two to a value
+#pragma unroll 1
+                for (int u = 0; u < 2 * kCap / kWave; ++u) {
+                    const int64_t q = 2 * (int64_t)a0 + u * kWave + lane, most = 2 * (int64_t)last + 1;
+                    wide_copy<4>(words + (q < most ? q : most), reinterpret_cast<int32_t *>(s_val) + u * kWave);
+                }
             }
         };
         stage(__builtin_amdgcn_readfirstlane(ra[0]), readlane(rb[0], kWave - 1));
@@ -267,8 +287,10 @@ __global__ __launch_bounds__(kCsrThreads, 6) void wide_a_kernel(const WideSlot *
             }
         }
         const int form = st[s].stage;
-        if (form > 0)
-            wide_stage_tile(s_raw, s_red, k, S, form - 1, src, y, dw);
+        if (form > 0 && ((reinterpret_cast<uintptr_t>(S.col) | reinterpret_cast<uintptr_t>(S.val)) & 15) == 0)
+            wide_stage_tile<true>(s_raw, s_red, k, S, form - 1, src, y, dw);
+        else if (form > 0)
+            wide_stage_tile<false>(s_raw, s_red, k, S, form - 1, src, y, dw);
         else
             csr_tile<double, double, 2, kCsrThreads, kCsrTile, 1, kCsrLateGather>(
                 s_raw, k, S.n, S.nnz, S.ntiles, S.rowptr, S.col, S.val, src, y, 1.0, 0.0, dw, S.part_a, S.csr_part);
