@@ -457,13 +457,16 @@ typedef struct {
     int32_t device;          /* HIP device of the server                        */
     int32_t max_slots;       /* concurrently resident systems                   */
     size_t hbm_budget_bytes; /* device memory for matrices and Krylov vectors   */
-    int32_t iters_per_tick;  /* CG iterations per system per tick (0 = adaptive) */
+    int32_t iters_per_tick;  /* iterations per tick of a one-work-group system
+                                (0 = adaptive); wide systems' ticks are sized
+                                by tick_us alone                               */
     int32_t tick_us;         /* adaptive budget: target tick length (0 = 2000)  */
     int32_t wide_min_rows;   /* systems with n >= this take the wide path
                                 (0 = 4097, as SPX_BATCH_AUTO; < 0 = never)       */
     int32_t debug_fail_tick; /* testing only: k > 0 makes the worker stop at its
                                 k-th tick as if a HIP call had failed (no device
-                                fault is involved); 0 = off                      */
+                                fault is involved), and wide ticks end after
+                                96 iterations; 0 = off                           */
     int32_t reserved0;
     int64_t inflight_bytes;  /* bound on the work admitted at once: the summed
                                 bytes one iteration of every resident system

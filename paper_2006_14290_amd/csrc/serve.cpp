@@ -51,9 +51,9 @@ constexpr int kBackfill = 8;
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 constexpr int kWideIters = 8;                    // wide iterations per graph launch
-// Fewest iterations of a wide tick under a fixed count per tick: at 10 us or
-// more each, a tick's synchronisation and read-back (about 25 us) stay below 3 %.
-constexpr int kWideFixedIters = 96;
+// Most iterations of a wide tick of a server that is to fail at a given tick:
+// its systems have to last that long (at 2 ms a tick they would not).
+constexpr int kWideDebugIters = 96;
 constexpr int kWideGrids[3] = {256, 1024, 4096};  // physical grids of the wide graphs
 // the state alternates between two buffers; an even count ends in the first
 static_assert(kWideIters % 2 == 0, "wide iterations per graph must be even");
@@ -665,12 +665,8 @@ void worker_main(spx_server *Sp)
             if (hipEventElapsedTime(&ms, S.ev_w0, S.ev_w1) == hipSuccess && ms > 0.f) {
                 const double tick_ms = (S.cfg.tick_us > 0 ? S.cfg.tick_us : 2000) * 1e-3;
                 const double per = ms / S.wide_launches;
-                // a fixed iteration count bounds the wide ticks too, but not
-                // below kWideFixedIters
-                const double most = S.cfg.iters_per_tick > 0
-                                        ? std::max(S.cfg.iters_per_tick, kWideFixedIters) / kWideIters
-                                        : 64.0;
-                S.wide_launches = (int)std::max(1.0, std::min(std::min(64.0, most), tick_ms / per));
+                const double most = S.cfg.debug_fail_tick > 0 ? kWideDebugIters / kWideIters : 64.0;
+                S.wide_launches = (int)std::max(1.0, std::min(most, tick_ms / per));
             }
         }
         {
