@@ -159,6 +159,7 @@ spx_status csr_partition_launch(const spx_matrix &A, int32_t *part, hipStream_t 
 // that 16-byte copies cannot read) keep the tile kernel.
 static int stage_len(const spx_matrix &A)
 {
+    if (A.csr_cb_tiles == kCsrNoStage) return 0;
     if (A.max_row_len <= 0 || A.nrows <= 0 || A.nnz < kStageMinNnz || A.nnz > INT32_MAX - kStageMinNnz) return 0;
     if (((reinterpret_cast<uintptr_t>(A.colidx) | reinterpret_cast<uintptr_t>(A.vals)) & 15) != 0) return 0;
     for (int len = 8; len <= 128; len *= 2)

@@ -14,6 +14,15 @@ constexpr int kRowU = 4;          // rows per subwarp in the row-per-subwarp ker
 constexpr int kRowMaxRows = 32768;  // larger matrices take the load-balanced kernel
 constexpr int64_t kStageMinNnz = 8192;  // staged-rows kernel: fewer entries take the load-balanced kernel
 
+// In csr_cb_tiles of a solver's own copy of a matrix (the solvers do not use the
+// column-blocked copy): not the staged-rows kernel. BiCG and BiCGSTAB set it:
+// their residuals jump about, so that sums in another order move the solution
+// at the tolerance, measured against the tile kernel's on convection-diffusion
+// systems by up to 4e-10 of its norm and 9e-8 of its RMS in one entry (BiCG,
+// 63^3 to 118^3 rows) and 1.2e-9 (BiCGSTAB). CG, GMRES and pipelined CG stay
+// below 6e-10 and 2e-9.
+constexpr int32_t kCsrNoStage = -1;
+
 inline int64_t csr_tiles(int64_t nnz) { return nnz > 0 ? ceil_div(nnz, kCsrTile) : 1; }
 
 struct KState;
