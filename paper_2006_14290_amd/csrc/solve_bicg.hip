@@ -181,7 +181,7 @@ spx_status bicg_run(const spx_matrix &A_in, const double *b, double *x, const So
     SPX_REQUIRE(c.fits(), SPX_ERR_ARG, "bicg: workspace of %zu bytes is too small (need %zu)", ws_bytes,
                 bicg_workspace(A_in, sp.precond));
     spx_matrix A = A_in;
-    A.csr_cb_tiles = kCsrNoStage;
+    if (n > kRowMaxRows) A.csr_cb_tiles = kCsrNoStage;
     *info = spx_solve_info{};
 
     SPX_HIP(hipEventRecord(env->join, user_stream));

@@ -197,7 +197,7 @@ spx_status bicgstab_run(const spx_matrix &A_in, const double *b, double *x, cons
     SPX_REQUIRE(c.fits(), SPX_ERR_ARG, "bicgstab: workspace of %zu bytes is too small (need %zu)", ws_bytes,
                 bicgstab_workspace(A_in, sp.precond));
     spx_matrix A = A_in;
-    A.csr_cb_tiles = kCsrNoStage;
+    if (n > kBicgstabStageRows) A.csr_cb_tiles = kCsrNoStage;
     *info = spx_solve_info{};
     SPX_HIP(hipEventRecord(env->join, user_stream));
     SPX_HIP(hipStreamWaitEvent(s, env->join, 0));

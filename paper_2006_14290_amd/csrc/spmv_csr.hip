@@ -54,15 +54,16 @@ __global__ __launch_bounds__(kThreads) void csr_spmv_kernel(
 // so every load instruction reads one contiguous stretch of col / val. The
 // first kSub entries of all kRowU rows are loaded before the first gather;
 // longer rows continue in a loop. Rows are reduced with DPP (fixed order).
-// A block does this once: what bounds it is the chain of its three dependent
-// loads (row pointer, column, x), so every further step of a block would add
-// the whole chain again (4,096 rows in 4 blocks of eight steps: 13.6 us; in
-// 32 blocks of one: 3.7).
+// A block does this `steps` times, over the rows that follow: once, as what
+// bounds it is the chain of its three dependent loads (row pointer, column, x)
+// and every further step adds the whole chain again (4,096 rows in 4 blocks of
+// eight steps: 13.6 us; in 32 blocks of one: 3.7); eight times where the sums'
+// order is to be kept (row_steps).
 template <typename V, typename X, int kEpi, int kSub>
 __global__ __launch_bounds__(kRowThreads) void csr_rows_kernel(
     int32_t nrows, int64_t nblocks, int64_t grid_padded, const int32_t *__restrict__ rowptr,
     const int32_t *__restrict__ col, const V *__restrict__ val, const X *__restrict__ x, X *__restrict__ y, X alpha,
-    X beta, const X *__restrict__ dot_with, X *__restrict__ dot_partials, KState *__restrict__ st)
+    X beta, const X *__restrict__ dot_with, X *__restrict__ dot_partials, KState *__restrict__ st, int steps)
 {
     if (st != nullptr && st->flag != kRunning) return;
     constexpr int kSubs = kRowThreads / kSub;
@@ -71,8 +72,9 @@ __global__ __launch_bounds__(kRowThreads) void csr_rows_kernel(
     if (blk >= nblocks) return;
     const int tid = threadIdx.x, sw = tid / kSub, sl = tid % kSub;
     X d1 = X(0), d2 = X(0);
-    {
-        const int64_t base = blk * kStep + sw;
+    for (int it = 0; it < steps; ++it) {
+        const int64_t base = (blk * steps + it) * kStep + sw;
+        if (base - sw >= nrows) break;  // uniform across the block
         int32_t a[kRowU], b[kRowU], c[kRowU];
         V v[kRowU];
 #pragma unroll
@@ -173,7 +175,8 @@ int csr_rows_sub(const spx_matrix &A)
     // row: 3,000 rows 3.8 / 3.5 us, 20,000 rows 5.1 / 6.1, 60,000 rows 9.8 /
     // 8.6. Below kStageMinNnz entries (1,089 rows of 5) 3.2 / 5.2.
     if (stage_len(A) > 0) return 0;
-    if (A.nrows <= 0 || A.nrows > kRowMaxRows || A.max_row_len <= 0 || A.nnz <= 0) return 0;
+    const int32_t most = A.csr_cb_tiles == kCsrNoStage ? 2 * kRowMaxRows : kRowMaxRows;
+    if (A.nrows <= 0 || A.nrows > most || A.max_row_len <= 0 || A.nnz <= 0) return 0;
     const int64_t mean = ceil_div(A.nnz, A.nrows);
     int sub = 4;
     while (sub < 64 && sub < mean) sub <<= 1;
@@ -224,13 +227,16 @@ static void stage_launch(const spx_matrix &A, int len, const X *x, X *y, X alpha
 #undef SPX_STAGE
 }
 
+// Steps of a block of the row-per-subwarp kernel.
+static int row_steps(const spx_matrix &A) { return A.nrows > kRowMaxRows ? 8 : 1; }
+
 int64_t csr_dot_parts(const spx_matrix &A)
 {
     const int len = stage_len(A);
     if (len > 0) return stage_grid(A, len);
     const int sub = csr_rows_sub(A);
     if (sub == 0) return csr_tiles(A.nnz);
-    return ceil_div(A.nrows, (int64_t)(kRowThreads / sub) * kRowU);
+    return ceil_div(A.nrows, (int64_t)(kRowThreads / sub) * kRowU * row_steps(A));
 }
 
 template <typename V, typename X>
@@ -252,7 +258,7 @@ spx_status csr_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X bet
 #define SPX_ROWS_LAUNCH(E, SUB)                                                                                      \
     csr_rows_kernel<V, X, E, SUB><<<(unsigned)grid, kRowThreads, 0, stream>>>(A.nrows, nblocks, grid, A.rowptr,         \
                                                                                A.colidx, val, x, y, alpha, beta,       \
-                                                                               dot_with, dot_partials, st)
+                                                                               dot_with, dot_partials, st, row_steps(A))
 #define SPX_ROWS_EPI(SUB)                                                                                            \
     if (epi == 2) SPX_ROWS_LAUNCH(2, SUB);                                                                           \
     else if (epi == 1) SPX_ROWS_LAUNCH(1, SUB);                                                                      \

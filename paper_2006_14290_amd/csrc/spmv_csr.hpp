@@ -15,13 +15,17 @@ constexpr int kRowMaxRows = 32768;  // larger matrices take the load-balanced ke
 constexpr int64_t kStageMinNnz = 8192;  // staged-rows kernel: fewer entries take the load-balanced kernel
 
 // In csr_cb_tiles of a solver's own copy of a matrix (the solvers do not use the
-// column-blocked copy): not the staged-rows kernel. BiCG and BiCGSTAB set it:
-// their residuals jump about, so that sums in another order move the solution
-// at the tolerance, measured against the tile kernel's on convection-diffusion
-// systems by up to 4e-10 of its norm and 9e-8 of its RMS in one entry (BiCG,
-// 63^3 to 118^3 rows) and 1.2e-9 (BiCGSTAB). CG, GMRES and pipelined CG stay
-// below 6e-10 and 2e-9.
+// column-blocked copy): not the staged-rows kernel, but the tile kernel and, up
+// to 2 kRowMaxRows rows, the row-per-subwarp kernel. BiCG sets it above
+// kRowMaxRows rows and BiCGSTAB above kBicgstabStageRows: their residuals jump
+// about, so that sums in another order move the solution at the tolerance, the
+// further the longer the solve. Staged or other sums against these, convection-
+// diffusion, one entry over the RMS and the norm: BiCG up to 32^3 rows 3e-8 and
+// 4e-10, 36^3 to 118^3 up to 9e-8 and 1e-9; BiCGSTAB up to 63^3 1e-10 of the
+// norm, 81^3 to 118^3 1.2e-9. CG, GMRES and pipelined CG: 2e-9 and 6e-10 at any
+// size.
 constexpr int32_t kCsrNoStage = -1;
+constexpr int64_t kBicgstabStageRows = 1 << 18;
 
 inline int64_t csr_tiles(int64_t nnz) { return nnz > 0 ? ceil_div(nnz, kCsrTile) : 1; }
 
