@@ -78,6 +78,17 @@ enum WideMode : int32_t {
     kWideDone = 3,
 };
 
+// The product phase deals its tiles out in runs of kWideRunTiles to the XCDs,
+// over whole groups of runs: a grid of wide_tile_grid(tiles) work-groups takes
+// one each (313 tiles, dealt over 384 places by 313 work-groups: 71 of these
+// took two, one after the other).
+constexpr int kWideRunTiles = 16;
+inline int64_t wide_tile_grid(int64_t tiles)
+{
+    const int64_t group = (int64_t)kWideRunTiles * kXcds;
+    return (tiles + group - 1) / group * group;
+}
+
 // Written by the host when the system is admitted. The product phase runs
 // the load-balanced CSR tile kernel over the system's ntiles tiles (its
 // partition in csr_part) or, when its rows are short and even, as many

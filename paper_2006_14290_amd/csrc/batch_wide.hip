@@ -45,7 +45,6 @@ constexpr int kWideWaves = kWideThreads / kWave;
 constexpr int kWideStageWaves = kCsrThreads / kWave;
 constexpr int kWideStageCap = 512;   // entries a wavefront stages at once
 constexpr int kWideStageForms = 5;   // rows of up to 8, 16, 32, 64, 128 entries
-constexpr int kWideRunTiles = 16;    // consecutive tiles on one XCD
 static_assert(kWideThreads == kCsrThreads, "both phases reduce with the same work-group");
 
 // kBytes per lane into LDS; see lds_copy16. Temporal: the solved systems'

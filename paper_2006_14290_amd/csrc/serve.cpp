@@ -1157,7 +1157,7 @@ spx_status cg_batch_run(spx_batch_system *sys, int32_t count, const BatchLayout 
                 }
             }
             m = WideMap{tot, nlisted, tta, 0};
-            grid = (int)std::min<int64_t>(std::max(tot, tta), 4096);
+            grid = (int)std::min<int64_t>(std::max<int64_t>(tot, wide_tile_grid(tta)), 4096);
             SPX_HIP(hipMemcpyAsync(wmap_dev, &m, sizeof(m), hipMemcpyHostToDevice, stream));
             SPX_HIP(hipMemcpyAsync(vb_dev, vb.data(), sizeof(int32_t) * vb.size(), hipMemcpyHostToDevice, stream));
             SPX_HIP(hipMemcpyAsync(ta_dev, ta.data(), sizeof(int32_t) * ta.size(), hipMemcpyHostToDevice, stream));

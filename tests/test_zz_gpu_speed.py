@@ -83,3 +83,17 @@ def test_transpose_of_mostly_empty_rows():
     print(f"copy {t_copy * 1e6:.1f} us, transpose {t * 1e6:.1f} us", flush=True)
     # 7 times the copy; every row walked by one wavefront took 3,600 times as long
     assert t < 100 * t_copy
+
+
+def test_batch_step_of_a_smaller_system():
+    """A wide step of a system of 220 tiles takes no longer than one of 256:
+    every tile has a work-group of its own."""
+    def steps(N):
+        A = spx.csr_from_host(S.poisson2d(N))
+        b = torch.rand(A.nrows, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(N))
+        return lambda: spx.cg_batch([A], [b], tol=1e-300, maxit=400)
+
+    t_small, t_large = seconds(steps(300), steps(324))
+    print(f"300^2 {t_small * 1e6:.1f} us, 324^2 {t_large * 1e6:.1f} us", flush=True)
+    # 0.98 of it per step; 1.25 with some work-groups taking two tiles in turn
+    assert t_small < 1.12 * t_large
