@@ -488,15 +488,19 @@ spx_status coo_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X bet
 // / together: 250,000 rows 43.6 / 39.2 us, 400,000 rows 55.3 / 71.5, 900,000
 // rows 141 / 155; 16 per row, 400,000 rows 39.7 / 47.6. Banded rows want them
 // together at any size (7-point 160^3 float64 74 / 70, float32 52 / 45,
-// binary16 45 / 40). Ragged rows (less than half of the slots stored) are
-// taken as scattered; otherwise every wavefront looks at its own rows, but for
-// binary16 rows of fewer than 8 entries, too short to pay for it.
+// binary16 45 / 40). Ragged rows (a quarter to half of the slots stored) are
+// taken as scattered; where padding is most of the stream the loads ahead
+// matter more (300,000 Zipf rows, float64 12.4 ms apart, 5.3 together);
+// otherwise every wavefront looks at its own rows, but
+// for binary16 rows of fewer than 8 entries, too short to pay for it.
 constexpr int32_t kEllLargeRows = 1 << 18;
 static EllMode ell_mode(const spx_matrix &A)
 {
     if (A.nrows <= kEllLargeRows) return kEllTogether;
     const int64_t stored = A.fmt == SPX_HYB ? A.nnz - A.coo_nnz : A.nnz;
-    if (2 * stored < (int64_t)A.ell_width * A.nrows) return kEllApart;
+    const int64_t slots = (int64_t)A.ell_width * A.nrows;
+    if (4 * stored < slots) return kEllTogether;
+    if (2 * stored < slots) return kEllApart;
     return A.val_type == SPX_F16 && A.ell_width < 8 ? kEllTogether : kEllByRows;
 }
 
@@ -727,10 +731,13 @@ __global__ __launch_bounds__(kSellThreads) void sellp64_spmv_kernel(int32_t nrow
 // 31.1), and in float64 where x is larger than one
 // XCD's L2 (rows of 5 to 45 random entries, 900,000 rows: 146.6 against 153;
 // 400,000 rows 64.2 against 63.2). Slices of fewer than 8 slot columns are too
-// short to pay for the look (5-point 1500^2: 37.7 us against 33.9).
+// short to pay for the look (5-point 1500^2: 37.7 us against 33.9), and where
+// padding is most of the stream the loads ahead matter more than the gathers
+// (Zipf rows, 3 % of the slots stored: 18.4 ms against 12.8).
 static bool sell_by_rows(const spx_matrix &A)
 {
-    if (A.slice_cols * kWave < int64_t(8) * A.nrows) return false;
+    const int64_t slots = A.slice_cols * kWave;
+    if (slots < int64_t(8) * A.nrows || 4 * A.nnz < slots) return false;
     return (A.nrows > (1 << 16) && A.nrows <= (1 << 17)) ||
            (A.val_type == SPX_F64 && A.ncols * (int64_t)sizeof(double) > kCooCachedX);
 }
