@@ -5,10 +5,12 @@
 // in device memory, so an iteration is a fixed sequence of kernel launches
 // with no host round trip and can be captured in a hipGraph. Reductions are
 // two-stage and deterministic: each work-group writes a partial to a fixed
-// slot; a one-work-group finish kernel sums the partials in a fixed order and
-// updates the scalars (one "finish" op per reduction). A flag in the state
-// stops every later kernel of a captured block of iterations as soon as the
-// solve has converged or failed.
+// slot; then either a one-work-group finish kernel sums the partials in a fixed
+// order and updates the scalars (one "finish" op per reduction), or every
+// work-group of the next kernel sums them itself in one order (CG's iteration,
+// the batched solves; block_sum_partials). A flag in the state stops every
+// later kernel of a captured block of iterations as soon as the solve has
+// converged or failed.
 #pragma once
 
 #include "common.hpp"

@@ -9,7 +9,10 @@
 //      (z = D^{-1} r is not stored; block Jacobi forms it in one more launch);
 //   3. x += alpha p, beta and the test ||r|| <= tol ||b||, p = z + beta p.
 // Every work-group of 2 and 3 sums the partials of the launch before it in
-// the same fixed order.
+// the same fixed order. Where the product leaves more than 4,096 of them (tile
+// kernel above 8.4 million entries, ELL above 1 or 2 million rows, SELL-P above
+// 1 million, the separate dot kernel above 4.2 million rows), one work-group
+// first sums them in a launch more (4.7 us).
 // Scalars never leave the device; a block of `check_every` iterations is
 // captured once into a hipGraph and replayed, and the host reads the state
 // only between replays. When the recursive residual passes, the true residual
@@ -76,7 +79,10 @@ __global__ __launch_bounds__(kVecThreads) void cg_init_kernel(int64_t n, const X
 // so all take the same decisions) instead of waiting for a one-work-group
 // finisher in between; the loads of their first vectors are in flight
 // meanwhile. At most kCgBlocks work-groups, so that the partials stay few
-// (1,024 values: 8 KB per work-group and row, from L2). What bounds them: the
+// (1,024 values: 8 KB per work-group and row, from L2). The product's are at
+// most kMaxParts; block Jacobi's r.z, one per 1,024 rows, are summed as they
+// are (first summed to one: 256^3, 16,384 of them, 716 us per iteration against
+// 719, 164^3 178.6 against 177.4). What bounds the kernels: the
 // vectors. Against the five-launch iteration (product, finisher, update,
 // finisher, direction), on one MI355X: Jacobi on the anisotropic 128^3 grid 82
 // -> 73 us per iteration (z is not stored: one vector pass less), the 64^3

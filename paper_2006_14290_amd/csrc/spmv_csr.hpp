@@ -1,4 +1,4 @@
-// spmv_csr.hpp -- launch interface of the load-balanced CSR product.
+// spmv_csr.hpp -- launch interface of the CSR product.
 #pragma once
 
 #include "common.hpp"
@@ -31,11 +31,6 @@ inline int64_t csr_tiles(int64_t nnz) { return nnz > 0 ? ceil_div(nnz, kCsrTile)
 
 struct KState;
 
-// y = alpha*A*x + beta*y for a CSR matrix with stored value type V and vector
-// type X. epi = 1: also sum_i y_i*dot_with_i; epi = 2: that and sum_i y_i^2,
-// one partial per tile in dot_partials[epi][csr_tiles(nnz)] (fixed order).
-// With a solver state st, a set st->flag skips the work (the caller reduces
-// the partials with finish_kernel).
 // Subwarp width of the row-per-subwarp kernel for A, or 0 when A takes
 // another kernel: the staged-rows kernel does not take A, A is small (at most
 // kRowMaxRows rows) and its rows are short and even (max_row_len known and at
@@ -58,6 +53,10 @@ inline int64_t csr_dot_parts_most(int64_t nrows, int64_t nnz)
 spx_status csr_partition_launch(const spx_matrix &A, int32_t *part, hipStream_t stream);
 inline int64_t csr_partition_bytes(int64_t nnz) { return 2 * (csr_tiles(nnz) + 1) * (int64_t)sizeof(int32_t); }
 
+// y = alpha*A*x + beta*y for a CSR matrix with stored value type V and vector
+// type X. epi = 1: also sum_i y_i*dot_with_i; epi = 2: that and sum_i y_i^2, in
+// epi rows of csr_dot_parts(A) partials (one per work-group, fixed order), which
+// the caller sums. With a solver state st, a set st->flag skips the work.
 template <typename V, typename X>
 spx_status csr_spmv_launch(const spx_matrix &A, const X *x, X *y, X alpha, X beta, const X *dot_with,
                            X *dot_partials, hipStream_t stream, int epi = 0, KState *st = nullptr, int op = 0);

@@ -39,6 +39,14 @@ __device__ inline int64_t lower_bound_wave(const int32_t *__restrict__ rowptr, i
     return lo + j;
 }
 
+// Bytes of LDS that csr_tile takes.
+template <typename V, typename X, int kTile, bool kLate>
+constexpr size_t csr_tile_lds()
+{
+    return (size_t)(kTile + kCsrSlack) *
+           (kLate ? sizeof(int32_t) + sizeof(typename acc_of<V>::type) : sizeof(X));
+}
+
 // Tile k of kTile nonzeros, processed by the calling work-group, which
 // owns the rows that start inside its tile: it reads their bounds from
 // the precomputed partition (or finds them with two wavefront searches),
@@ -50,13 +58,6 @@ __device__ inline int64_t lower_bound_wave(const int32_t *__restrict__ rowptr, i
 // and sum_i y_i*y_i. With a solver state the sums are reduced across tiles
 // (deterministically, one partial per tile at dot_partials[j * ntiles + k]).
 // s_raw: csr_tile_lds<V, X, kTile, kLate>() bytes of LDS, 16-byte aligned.
-template <typename V, typename X, int kTile, bool kLate>
-constexpr size_t csr_tile_lds()
-{
-    return (size_t)(kTile + kCsrSlack) *
-           (kLate ? sizeof(int32_t) + sizeof(typename acc_of<V>::type) : sizeof(X));
-}
-
 template <typename V, typename X, int kEpi, int kThreads, int kTile, int kVec, bool kLate>
 __device__ __forceinline__ void csr_tile(unsigned char *s_raw, int64_t k, int32_t nrows, int64_t nnz, int64_t ntiles,
                                          const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
